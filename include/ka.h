@@ -55,7 +55,9 @@ enum ka_method { KA_GALERKIN_IBQ = 0,   /* Galerkin with interpolation-based qua
 enum ka_domain { KA_BOX = 0, KA_QUARTER_ANNULUS = 1, KA_NURBS = 2 /* general single-patch NURBS volume */ };
 enum ka_kernel { KA_GAUSSIAN = 0, /* sigma^2 exp(-|x-y|_2^2 / ell^2) */
                  KA_EXP_L1 = 1    /* sigma^2 exp(-|x-y|_1 / ell)     */ };
-enum ka_precision { KA_FP32 = 0,  /* FP32 kernel tiles, FP32 MFMA contraction        */
+enum ka_precision { KA_FP32 = 0,  /* FP32 kernel tiles, FP32 MFMA contraction; large
+                                     products contract pairs of FP16 parts that hold
+                                     FP32's significand (3 FP16 MFMAs, FP32 accumulation) */
                     KA_BF16X3 = 1 /* FP32 tiles split hi+lo into BF16, 3 BF16 MFMAs,
                                      FP32 accumulation                               */ };
 enum ka_form { KA_A = 0,          /* the covariance matrix A itself                  */
@@ -245,8 +247,10 @@ int ka_eigs(ka_problem* p, int M, double tol, int maxit, double* lambda_host, in
  * precision KA_FP32 or KA_BF16X3.  Scratch from `work_dev` (work_bytes,
  * 16-byte aligned): the split-K partial sums (nsplit * nr * b * 4 bytes when
  * the columns are split) and, for KA_BF16X3, Y split into hi/lo BF16 parts
- * (ceil(nc / 64) * 64 * b * 4 bytes); pass ka_gamma_workspace() bytes.
- * Async on `stream`. */
+ * (ceil(nc / 64) * 64 * b * 4 bytes).  Large KA_FP32 products also split Y and
+ * the points into FP16 parts (about (4 b + 64) nc bytes) and then run 1.5 to 3
+ * times as fast; with less scratch than that they run on the FP32 matrix cores.
+ * Pass ka_gamma_workspace() bytes.  Async on `stream`. */
 int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, int64_t nr,
                    const float* xc_dev, int64_t nc, const float* Y_dev, int b, float* Z_dev,
                    int precision, void* work_dev, size_t work_bytes, void* stream);

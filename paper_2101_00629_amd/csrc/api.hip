@@ -32,16 +32,17 @@ int fail(int code, const std::string& msg) {
       return fail(KA_ERR_HIP, std::string(#expr) + ": " + hipGetErrorString(e_));       \
   } while (0)
 
-float kernel_coord_scale(int kernel, double ell) {
-  if (std::isinf(ell)) return 0.0f;
-  const double log2e = 1.4426950408889634074;
-  return kernel == KA_GAUSSIAN ? (float)(std::sqrt(log2e) / ell) : (float)(log2e / ell);
-}
-
 static double coord_scale64(int kernel, double ell) {
   if (std::isinf(ell)) return 0.0;
   const double log2e = 1.4426950408889634074;
   return kernel == KA_GAUSSIAN ? std::sqrt(log2e) / ell : log2e / ell;
+}
+
+float kernel_coord_scale(int kernel, double ell, float* lo) {
+  const double s = coord_scale64(kernel, ell);
+  const float hi = (float)s;
+  *lo = std::isfinite(hi) ? (float)(s - (double)hi) : 0.0f;
+  return hi;
 }
 
 // ---------------------------------------------------------------------------
@@ -481,8 +482,11 @@ int gamma_step(Problem* P, const float* Y, float* Z, hipStream_t s) {
   g.Y = Y;
   g.Z = Z;
   g.partial = P->gpart;
-  g.ys = nullptr;   // launch_gamma places it in the scratch
+  g.ys = nullptr;   // launch_gamma places these in the scratch
+  g.yup = nullptr;
+  g.gbox = nullptr;
   g.coord_scale = P->coord_scale;
+  g.coord_scale_lo = 0.0f;   // prescaled in FP64
   g.out_scale = P->out_scale;
   g.nsplit = 1;
   g.cols_per_split = 0;
@@ -501,7 +505,7 @@ int gamma_step(Problem* P, const float* Y, float* Z, hipStream_t s) {
     }
     HIP_TRY(hipEventRecord(e0, s));
   }
-  HIP_TRY(launch_gamma(g, P->d.kernel, P->b, P->d.precision, s));
+  HIP_TRY(launch_gamma(g, P->gpart_bytes, P->d.kernel, P->b, P->d.precision, s));
   const double pairs = (double)P->n_rows * (double)P->n_cols;
   P->pairs_total += pairs;
   if (P->profile) {
@@ -606,6 +610,7 @@ GammaLaunch gamma_job(Problem* P) {
   g.Z = P->w32a;
   g.partial = P->gpart;
   g.coord_scale = P->coord_scale;
+  g.coord_scale_lo = 0.0f;   // prescaled in FP64
   g.out_scale = P->out_scale;
   const GammaPlan gp = gamma_plan(g.nr, g.nc, P->b, P->d.precision);
   g.nsplit = gp.nsplit;

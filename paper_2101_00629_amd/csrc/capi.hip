@@ -83,7 +83,7 @@ int ka_eigs(ka_problem* p, int M, double tol, int maxit, double* lambda_host, in
 
 size_t ka_gamma_workspace(int64_t nr, int64_t nc, int b, int precision) {
   if (nr <= 0 || nc <= 0) return 0;
-  return gamma_plan(nr, nc, b, precision).work_bytes;
+  return gamma_plan(nr, nc, b, precision).stated_bytes;
 }
 
 int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, int64_t nr, const float* xc_dev,
@@ -98,7 +98,7 @@ int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, in
   if (!xr_dev || !Z_dev || (nc > 0 && (!xc_dev || !Y_dev))) return fail(KA_ERR_ARG, "NULL pointer");
   if (((uintptr_t)Y_dev & 15) != 0) return fail(KA_ERR_ARG, "Y must be 16-byte aligned");
   const GammaPlan gp = gamma_plan(nr, nc, b, precision);
-  if (gp.work_bytes > work_bytes || (gp.work_bytes > 0 && !work_dev))
+  if (gp.base_bytes > work_bytes || (gp.base_bytes > 0 && !work_dev))
     return fail(KA_ERR_ARG, "workspace too small (see ka_gamma_workspace)");
   if (((uintptr_t)work_dev & 15) != 0) return fail(KA_ERR_ARG, "workspace must be 16-byte aligned");
   GammaLaunch g;
@@ -113,13 +113,13 @@ int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, in
   g.Z = Z_dev;
   g.partial = (float*)work_dev;
   g.ys = nullptr;   // launch_gamma places it in the workspace
-  g.coord_scale = kernel_coord_scale(kernel, ell);
+  g.coord_scale = kernel_coord_scale(kernel, ell, &g.coord_scale_lo);
   g.out_scale = (float)(sigma * sigma);
   g.nsplit = 1;
   g.cols_per_split = 0;
   g.row_blocks = 0;
   g.xcd_splits = 0;   // launch_gamma fills the plan
-  const hipError_t e = launch_gamma(g, kernel, b, precision, (hipStream_t)stream);
+  const hipError_t e = launch_gamma(g, work_dev ? work_bytes : 0, kernel, b, precision, (hipStream_t)stream);
   if (e != hipSuccess) return fail(KA_ERR_HIP, std::string("kernel product launch: ") + hipGetErrorString(e));
   return KA_OK;
 }

@@ -55,8 +55,8 @@ int ka_gamma_apply_static(int kernel, double sigma, double ell, const float* xr_
   if (!xr_dev || !Z_dev || (nc > 0 && (!xc_dev || !Y_dev))) return fail(KA_ERR_ARG, "NULL pointer");
   if (((uintptr_t)Y_dev & 15) != 0) return fail(KA_ERR_ARG, "Y must be 16-byte aligned");
   const GammaPlan gp = gamma_plan(nr, nc, b, precision);
-  if (gp.work_bytes > kStaticScratchBytes)
-    return fail(KA_ERR_ARG, "product needs " + std::to_string(gp.work_bytes) + " scratch bytes, more than the " +
+  if (gp.base_bytes > kStaticScratchBytes)
+    return fail(KA_ERR_ARG, "product needs " + std::to_string(gp.base_bytes) + " scratch bytes, more than the " +
                                 std::to_string(kStaticScratchBytes) + " of the static scratch (use ka_gamma_apply)");
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return fail(KA_ERR_HIP, "no current device");
@@ -74,13 +74,13 @@ int ka_gamma_apply_static(int kernel, double sigma, double ell, const float* xr_
   g.Z = Z_dev;
   g.partial = (float*)work;   // every entry a launch reads is written by the same launch first
   g.ys = nullptr;             // launch_gamma places it in the scratch
-  g.coord_scale = kernel_coord_scale(kernel, ell);
+  g.coord_scale = kernel_coord_scale(kernel, ell, &g.coord_scale_lo);
   g.out_scale = (float)(sigma * sigma);
   g.nsplit = 1;
   g.cols_per_split = 0;
   g.row_blocks = 0;
   g.xcd_splits = 0;
-  const hipError_t e = launch_gamma(g, kernel, b, precision, (hipStream_t)stream);
+  const hipError_t e = launch_gamma(g, kStaticScratchBytes, kernel, b, precision, (hipStream_t)stream);
   if (e != hipSuccess) return fail(KA_ERR_HIP, std::string("kernel product launch: ") + hipGetErrorString(e));
   return KA_OK;
 }

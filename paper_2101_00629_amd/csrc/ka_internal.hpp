@@ -23,8 +23,13 @@ struct GammaLaunch {
   const float* Y;         // nc x b, b contiguous
   float* Z;               // nr x b, b contiguous
   float* partial;         // split-K scratch, nsplit * nr * b floats
-  uint4* ys;              // BF16X3: Y split into hi/lo BF16 MFMA fragments (gamma_split_y); filled by launch_gamma
+  uint4* ys;              // split products: Y as hi/lo BF16 or FP16 MFMA fragments; filled by launch_gamma
+  uint4* xs;              // split FP16: Gram operands of the column points; filled by launch_gamma
+  float* yup;             // split FP16: scale exponent of each vector in each column group; filled by launch_gamma
+  float* gbox;            // split FP16: bounding box and flag of each column group; filled by launch_gamma
+  int64_t ngroups;        // split FP16: column groups; filled by launch_gamma
   float coord_scale;      // applied to every coordinate on load
+  float coord_scale_lo;   // what coord_scale leaves of the FP64 scale (split FP16)
   float out_scale;        // sigma^2
   int nsplit;             // filled by launch_gamma
   int64_t cols_per_split; // filled by launch_gamma
@@ -39,7 +44,10 @@ struct GammaPlan {
   int64_t cols_per_split;
   size_t partial_bytes;
   size_t ysplit_bytes;    // BF16X3: pre-split Y, ceil(nc / 64) * 64 * b * 4 bytes; 0 for FP32
-  size_t work_bytes;      // scratch of one product: partials (256-byte aligned), then the pre-split Y
+  size_t base_bytes;      // least scratch: partials (256-byte aligned), then the pre-split Y
+  size_t work_bytes;      // scratch of the fastest path at this precision (base_bytes or more)
+  size_t stated_bytes;    // ka_gamma_workspace: enough for it at either precision
+  bool f16;               // FP32: contraction on the FP16 matrix cores where the scratch holds work_bytes
   int xcd_splits;         // 0, or the split count rounded up to the XCD count (grouped grid)
 };
 
@@ -63,8 +71,13 @@ hipError_t launch_gamma_batch(const GammaJob* jobs_dev, const GammaItem* items_d
 hipError_t launch_gamma_reduce(const float* partial, int nsplit, int64_t n, float* Z, hipStream_t s);
 // BF16X3 pre-pass of a batched launch: splits Y of jobs [0, n_jobs) into their ys arrays.
 hipError_t launch_gamma_split_jobs(const GammaJob* jobs_dev, int n_jobs, int b, hipStream_t s);
-hipError_t launch_gamma(GammaLaunch a, int kernel, int b, int precision, hipStream_t s);
-float kernel_coord_scale(int kernel, double ell);
+// a.partial: scratch of work_bytes bytes, at least the plan's base_bytes
+hipError_t launch_gamma(GammaLaunch a, size_t work_bytes, int kernel, int b, int precision, hipStream_t s);
+// split FP16 (gamma_f16x3.hip): scratch for Y, its placement, pre-pass and product
+size_t gamma_f16x3_bytes(int64_t nc, int b);
+void gamma_f16x3_place(GammaLaunch& a, int b, void* work);
+hipError_t launch_gamma_f16x3(const GammaLaunch& a, int kernel, int b, dim3 grid, hipStream_t s);
+float kernel_coord_scale(int kernel, double ell, float* lo);
 
 // ---- Kronecker mode products -------------------------------------------
 // A tensor with dims (n1, n2, n3) per vector and nv vectors.  Layout
