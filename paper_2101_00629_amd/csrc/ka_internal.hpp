@@ -238,6 +238,7 @@ struct Problem {
   size_t kl_bytes = 0;
   double* kl_omega = nullptr;
   double* kl_Eq[3] = {nullptr, nullptr, nullptr};
+  double* kl_EqT[3] = {nullptr, nullptr, nullptr};
   int kl_mq[3] = {0, 0, 0};
 };
 

@@ -64,16 +64,25 @@ __global__ void wdot_final_kernel(const double* __restrict__ part, int nchunk, i
   out[i] = s;
 }
 
-// XiT[s + k S] = f[k] Xi[k + s ldxi]: the draws scaled and laid out sample-fastest.
-__global__ void xi_scale_kernel(const double* __restrict__ Xi, int64_t ldxi, int K, int S,
-                                const double* __restrict__ f, double* __restrict__ XiT) {
+// XiT[s + k Sp] = sqrt(lambda[k] / norm2[k]) Xi[k + s ldxi] for k < Kp, s < Sp,
+// zero past K and S: the draws scaled, laid out sample-fastest and padded to
+// whole MFMA tiles.  A norm that is not positive and finite sets *bad.
+__global__ void xi_scale_kernel(const double* __restrict__ Xi, int64_t ldxi, int K, int S, int Kp, int64_t Sp,
+                                const double* __restrict__ lambda, const double* __restrict__ norm2,
+                                double* __restrict__ XiT, double* __restrict__ bad) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)K * S) return;
-  const int s = (int)(id % S), k = (int)(id / S);
-  XiT[s + (int64_t)k * S] = f[k] * Xi[k + (int64_t)s * ldxi];
+  if (id >= (int64_t)Kp * Sp) return;
+  const int s = (int)(id % Sp), k = (int)(id / Sp);
+  double v = 0.0;
+  if (k < K) {
+    const double n = norm2[k];
+    if (!(n > 0.0) || !(n - n == 0.0)) *bad = 1.0;
+    if (s < S) v = sqrt(lambda[k] / n) * Xi[k + (int64_t)s * ldxi];
+  }
+  XiT[id] = v;
 }
 
-// F[p + s ldf] = mu + sum_k Phi[p + k ldp] XiT[s + k S].
+// F[p + s ldf] = mu + sum_k Phi[p + k ldp] XiT[s + k Sp].
 //
 // v_mfma_f64_16x16x4f64 with A = XiT^T (rows: samples) and B = Phi^T
 // (columns: points), so a lane's 16 consecutive points land in consecutive
@@ -84,67 +93,107 @@ __global__ void xi_scale_kernel(const double* __restrict__ Xi, int64_t ldxi, int
 // are dealt to the 8 XCDs round-robin by id; the id mapping gives each XCD
 // whole point-tiles (all their sample tiles back to back), so a tile of Phi
 // is fetched from HBM into one L2 once.
+//
+// Bound by its stores and the FP64 matrix cores alike: a 64^3 grid, 1000
+// samples and M = 50 write 2.1 GB (0.37 ms at the 5.7 TB/s of a plain fill) and
+// take 2.7e10 flops (0.35 ms at 78 TFLOP/s).  A workgroup therefore walks
+// `tiles` sample tiles of its points in one pipeline of k-steps: operands are
+// requested two steps ahead across the tile ends, and a tile's stores go out
+// while the next one's MFMAs run.  Operands past the edges are read at the edge
+// and meet zeros of XiT, so no load is conditional.  The fields are not read
+// again here: their stores are non-temporal.  At that size, with the products
+// around it: 2846 us with conditional loads in each step and one tile per
+// workgroup, 1095 us with unconditional ones ahead, 1024 us with the
+// non-temporal stores, 982 / 959 / 950 / 926 us walking 1 / 2 / 4 / 8 tiles.
 constexpr int kU = 2, kT = 4;                       // 16 x 16 MFMA tiles per wave: samples x points
 constexpr int kFS = 2 * 16 * kU, kFP = 2 * 16 * kT;  // workgroup tile (2 x 2 waves)
+constexpr int kMaxTiles = 8;                         // sample tiles per workgroup
 
-__global__ __launch_bounds__(256) void kl_field_kernel(const double* __restrict__ Phi, int64_t ldp, int64_t P,
-                                                       const double* __restrict__ XiT, int S, int K, double mu,
-                                                       double* __restrict__ F, int64_t ldf, int64_t n_pt, int n_st) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void kl_field_kernel(const double* __restrict__ Phi, int64_t ldp, int64_t P, const double* __restrict__ XiT, int S,
+                     int64_t Sp, int K, double mu, const double* __restrict__ bad, double* __restrict__ F, int64_t ldf,
+                     int64_t n_pt, int n_sg, int tiles) {
   const int64_t L = blockIdx.x;
   const int64_t j = L / 8;
-  const int64_t pt = (L % 8) + 8 * (j / n_st);
-  const int st = (int)(j % n_st);
-  if (pt >= n_pt) return;
+  const int64_t pt = (L % 8) + 8 * (j / n_sg);
+  const int sg = (int)(j % n_sg);
+  if (pt >= n_pt || *bad != 0.0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int64_t p0 = pt * kFP + (wave & 1) * (16 * kT);
-  const int s0 = st * kFS + (wave >> 1) * (16 * kU);
-  d4v acc[kU][kT];
+  const int s_first = sg * tiles * kFS + (wave >> 1) * (16 * kU);
+  const int left = (int)(Sp / kFS) - sg * tiles;
+  const int ntile = left < tiles ? left : tiles;
+  int64_t po[kT];
 #pragma unroll
-  for (int u = 0; u < kU; ++u)
+  for (int t = 0; t < kT; ++t) {
+    const int64_t p = p0 + 16 * t + li;
+    po[t] = p < P ? p : P - 1;
+  }
+  const int nk = (K + 3) / 4;
+  // operands of the next k-step in turn (rows 4 c + lk of XiT^T and Phi^T),
+  // past the last tile's end those of its first steps again
+  int lc = 0, lt = 0;
+  auto load = [&](double (&a)[kU], double (&b)[kT]) {
+    const int k = 4 * lc + lk;
+    const double* x = XiT + k * Sp + (s_first + lt * kFS + li);
 #pragma unroll
-    for (int t = 0; t < kT; ++t) acc[u][t] = (d4v){0.0, 0.0, 0.0, 0.0};
-  // operands of k-step k0 (rows k0 + lk of XiT^T and Phi^T); zero past the edges
-  auto load = [&](int k0, double* a, double* b) {
-    const int k = k0 + lk;
+    for (int u = 0; u < kU; ++u) a[u] = x[16 * u];
+    const double* f = Phi + (int64_t)(k < K ? k : K - 1) * ldp;
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int s = s0 + 16 * u + li;
-      a[u] = (k < K && s < S) ? XiT[s + (int64_t)k * S] : 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < kT; ++t) {
-      const int64_t p = p0 + 16 * t + li;
-      b[t] = (k < K && p < P) ? Phi[p + (int64_t)k * ldp] : 0.0;
+    for (int t = 0; t < kT; ++t) b[t] = f[po[t]];
+    if (++lc == nk) {
+      lc = 0;
+      if (lt + 1 < ntile) ++lt;
     }
   };
-  double a[kU], b[kT];
-  load(0, a, b);
-  for (int k0 = 0; k0 < K; k0 += 4) {
-    // the next step's operands are requested before this step's MFMAs; the
-    // scheduling barrier keeps the compiler from sinking the loads
-    double an[kU], bn[kT];
-    load(k0 + 4, an, bn);
-    __builtin_amdgcn_sched_barrier(0);
+  d4v acc[kU][kT];
+  auto step = [&](const double (&a)[kU], const double (&b)[kT]) {
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
       for (int t = 0; t < kT; ++t) acc[u][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[t], acc[u][t], 0, 0, 0);
+  };
+  double a0[kU], b0[kT], a1[kU], b1[kT];
+  load(a0, b0);
+  load(a1, b1);
+  for (int tile = 0; tile < ntile; ++tile) {
 #pragma unroll
-    for (int u = 0; u < kU; ++u) a[u] = an[u];
+    for (int u = 0; u < kU; ++u)
 #pragma unroll
-    for (int t = 0; t < kT; ++t) b[t] = bn[t];
-  }
+      for (int t = 0; t < kT; ++t) acc[u][t] = (d4v){mu, mu, mu, mu};
+    // each step's operands are replaced as soon as its MFMAs are issued; the
+    // scheduling barriers keep the compiler from sinking the loads
+    int c = 0;
+    for (; c + 2 <= nk; c += 2) {
+      step(a0, b0);
+      load(a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      step(a1, b1);
+      load(a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (c < nk) {
+      step(a0, b0);
 #pragma unroll
-  for (int u = 0; u < kU; ++u)
+      for (int u = 0; u < kU; ++u) a0[u] = a1[u];
 #pragma unroll
-    for (int t = 0; t < kT; ++t)
+      for (int t = 0; t < kT; ++t) b0[t] = b1[t];
+      load(a1, b1);
+    }
+    const int s0 = s_first + tile * kFS + lk;
+    double* row = F + (int64_t)s0 * ldf + p0 + li;
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int s = s0 + 16 * u + lk + 4 * r;
-        const int64_t p = p0 + 16 * t + li;
-        if (s < S && p < P) F[p + (int64_t)s * ldf] = mu + acc[u][t][r];
+#pragma unroll
+        for (int t = 0; t < kT; ++t)
+          if (s0 + 16 * u + 4 * r < S && p0 + 16 * t + li < P)
+            __builtin_nontemporal_store(acc[u][t][r], row + 16 * t);
+        row += 4 * ldf;
       }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -165,7 +214,7 @@ struct KlArena {
 };
 
 ModeArgs col_mode(const double* in, int64_t in_ld, double* out, int64_t out_ld, const int dims[3], int mode, int m,
-                  const double* mat, int nv) {
+                  const double* mat, const double* matT, int nv) {
   ModeArgs a;
   a.in = in;
   a.in_layout = LAYOUT_COL;
@@ -177,22 +226,22 @@ ModeArgs col_mode(const double* in, int64_t in_ld, double* out, int64_t out_ld, 
   a.mode = mode;
   a.m = m;
   a.mat = mat;
-  a.matT = nullptr;   // column-major layouts read mat
+  a.matT = matT;
   a.nv = nv;
   a.out_scale = nullptr;
   return a;
 }
 
-// (E_3 x E_2 x E_1) V[:, c0 : c0 + nv] -> out (column-major, ld = m0 m1 m2)
-hipError_t kron_eval(const int n[3], const int m[3], double* const E[3], const double* V, int64_t ldv, int nv,
-                     double* t1, double* t2, double* out, int64_t ld_out, hipStream_t s) {
+// (E_3 x E_2 x E_1) V[:, 0 : nv] -> out (column-major, ld = m0 m1 m2); ET: the transposes
+hipError_t kron_eval(const int n[3], const int m[3], double* const E[3], double* const ET[3], const double* V,
+                     int64_t ldv, int nv, double* t1, double* t2, double* out, int64_t ld_out, hipStream_t s) {
   const int d0[3] = {n[0], n[1], n[2]};
   const int d1[3] = {m[0], n[1], n[2]};
   const int d2[3] = {m[0], m[1], n[2]};
-  hipError_t e = launch_mode_f64(col_mode(V, ldv, t1, (int64_t)m[0] * n[1] * n[2], d0, 0, m[0], E[0], nv), s);
-  if (e == hipSuccess)
-    e = launch_mode_f64(col_mode(t1, (int64_t)m[0] * n[1] * n[2], t2, (int64_t)m[0] * m[1] * n[2], d1, 1, m[1], E[1], nv), s);
-  if (e == hipSuccess) e = launch_mode_f64(col_mode(t2, (int64_t)m[0] * m[1] * n[2], out, ld_out, d2, 2, m[2], E[2], nv), s);
+  const int64_t l1 = (int64_t)m[0] * n[1] * n[2], l2 = (int64_t)m[0] * m[1] * n[2];
+  hipError_t e = launch_mode_f64(col_mode(V, ldv, t1, l1, d0, 0, m[0], E[0], ET[0], nv), s);
+  if (e == hipSuccess) e = launch_mode_f64(col_mode(t1, l1, t2, l2, d1, 1, m[1], E[1], ET[1], nv), s);
+  if (e == hipSuccess) e = launch_mode_f64(col_mode(t2, l2, out, ld_out, d2, 2, m[2], E[2], ET[2], nv), s);
   return e;
 }
 
@@ -270,9 +319,26 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
       omega[i] = wq[0][a1] * wq[1][a2] * wq[2][a3] * J / (W * W);
     }
   }
-  // per-point scale of phi on the grid: Galerkin 1/sqrt|det DF|, NURBS collocation 1/W
+  // per-point scale of phi on the grid: Galerkin 1/sqrt|det DF|, NURBS
+  // collocation 1/W.  On the closed-form domains |det DF| is a product of
+  // functions of one coordinate each (the box: a constant; the quarter annulus:
+  // r(eta) |C x C'|(xi)), taken into the rows of the univariate matrices.
+  if (!coll && !nurbs) {
+    auto det = [&](int k, double x) {
+      double xh[3] = {0.5, 0.5, 0.5}, y[3], J;
+      if (k >= 0) xh[k] = x;
+      geo.eval(xh, y, &J, nullptr);
+      return J;
+    };
+    const double J0 = det(-1, 0.0);
+    for (int k = 0; k < 3; ++k)
+      for (int a = 0; a < Eg[k].rows; ++a) {
+        const double f = 1.0 / std::sqrt(k == 0 ? det(k, grid[k][a]) : det(k, grid[k][a]) / J0);
+        for (int j = 0; j < Eg[k].cols; ++j) Eg[k](a, j) *= f;
+      }
+  }
   std::vector<double> gscale;
-  if (!coll || nurbs) {
+  if (nurbs) {
     gscale.resize(Pts);
     for (int64_t i = 0; i < Pts; ++i) {
       const int64_t a1 = i % mg[0], a2 = (i / mg[0]) % mg[1], a3 = i / ((int64_t)mg[0] * mg[1]);
@@ -296,29 +362,41 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
   if (coll && !P->kl_omega) {
     for (int k = 0; k < 3; ++k) {
       P->kl_Eq[k] = keep(to_rows(Eq[k]));
-      if (!P->kl_Eq[k]) return fail(KA_ERR_OOM, "device allocation failed in ka_kl_sample");
+      P->kl_EqT[k] = P->kl_Eq[k] ? keep(to_rows(transpose(Eq[k]))) : nullptr;
+      if (!P->kl_EqT[k]) return fail(KA_ERR_OOM, "device allocation failed in ka_kl_sample");
       P->kl_mq[k] = mq[k];
     }
     P->kl_omega = keep(omega);
     if (!P->kl_omega) return fail(KA_ERR_OOM, "device allocation failed in ka_kl_sample");
   }
-  // this call's workspace
-  const int chunk = std::min(M, 32);
+  // this call's workspace; the host's data (grid matrices and transposes,
+  // eigenvalues, the cleared flag) go up in one copy
+  const int chunk = std::min(M, 128);
   const int64_t tq = std::max((int64_t)mq[0] * n[1] * n[2], (int64_t)mq[0] * mq[1] * n[2]);
   const int64_t tg = std::max((int64_t)mg[0] * n[1] * n[2], (int64_t)mg[0] * mg[1] * n[2]);
   const int64_t clen = std::max<int64_t>(8192, (Q + 255) / 256);
   const int nchunk = (int)((Q + clen - 1) / clen);
-  std::vector<std::vector<double>> Eg_rows(3);
-  KlArena ar;
-  size_t iEg[3];
+  const int Kp = (M + 3) / 4 * 4;
+  const int64_t Sp = ((int64_t)nsamples + kFS - 1) / kFS * kFS;
+  std::vector<double> up;
+  size_t oE[3], oET[3];
   for (int k = 0; k < 3; ++k) {
-    Eg_rows[k] = to_rows(Eg[k]);
-    iEg[k] = ar.add(Eg_rows[k].size());
+    const Mat ET = transpose(Eg[k]);
+    oE[k] = up.size();
+    up.insert(up.end(), Eg[k].a.begin(), Eg[k].a.end());
+    oET[k] = up.size();
+    up.insert(up.end(), ET.a.begin(), ET.a.end());
   }
+  const size_t olam = up.size();
+  up.insert(up.end(), lambda_host, lambda_host + M);
+  const size_t obad = up.size();
+  up.push_back(0.0);
+  KlArena ar;
+  const size_t iup = ar.add(up.size());
   const size_t it1 = ar.add((size_t)std::max(tq, tg) * chunk), it2 = ar.add((size_t)std::max(tq, tg) * chunk);
   const size_t iUq = ar.add((size_t)Q * chunk), ipart = ar.add((size_t)nchunk * chunk), inorm = ar.add(M);
-  const size_t iPhi = ar.add((size_t)Pts * M), igs = ar.add(gscale.size()), ifac = ar.add(M);
-  const size_t iXi = ar.add((size_t)M * nsamples);
+  const size_t iPhi = ar.add((size_t)Pts * M), igs = ar.add(gscale.size());
+  const size_t iXi = ar.add((size_t)Kp * Sp);
   if (P->kl_bytes < ar.total) {
     if (P->kl_buf) {
       (void)hipStreamSynchronize(s);
@@ -333,12 +411,14 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
     P->kl_bytes = ar.total;
   }
   auto at = [&](size_t i) { return (double*)((char*)P->kl_buf + ar.off[i]); };
-  double* Eqd[3];
-  double* Egd[3];
+  double* up_d = at(iup);
+  HIP_TRY(hipMemcpyAsync(up_d, up.data(), up.size() * sizeof(double), hipMemcpyHostToDevice, s));
+  double *Eqd[3], *EqTd[3], *Egd[3], *EgTd[3];
   for (int k = 0; k < 3; ++k) {
-    Eqd[k] = coll ? P->kl_Eq[k] : P->Zk[k];   // Galerkin: Z v with the mass matrices
-    Egd[k] = at(iEg[k]);
-    HIP_TRY(hipMemcpyAsync(Egd[k], Eg_rows[k].data(), Eg_rows[k].size() * sizeof(double), hipMemcpyHostToDevice, s));
+    Eqd[k] = coll ? P->kl_Eq[k] : P->Zk[k];    // Galerkin: Z v with the mass matrices (symmetric)
+    EqTd[k] = coll ? P->kl_EqT[k] : P->Zk[k];
+    Egd[k] = up_d + oE[k];
+    EgTd[k] = up_d + oET[k];
   }
   double* t1 = at(it1);
   double* t2 = at(it2);
@@ -349,41 +429,40 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
   double* Phi = at(iPhi);
   double* gscale_d = gscale.empty() ? nullptr : at(igs);
   if (gscale_d) HIP_TRY(hipMemcpyAsync(gscale_d, gscale.data(), gscale.size() * sizeof(double), hipMemcpyHostToDevice, s));
-  double* fac_d = at(ifac);
   double* XiT = at(iXi);
 
   for (int c0 = 0; c0 < M; c0 += chunk) {
     const int nv = std::min(chunk, M - c0);
     const double* Vc = V_dev + (int64_t)c0 * ldv;
     // collocation: phi at the Gauss points, norms^2 = sum omega phi^2; Galerkin: Z v, norms^2 = v^T Z v
-    HIP_TRY(kron_eval(n, mq, Eqd, Vc, ldv, nv, t1, t2, Uq, Q, s));
+    HIP_TRY(kron_eval(n, mq, Eqd, EqTd, Vc, ldv, nv, t1, t2, Uq, Q, s));
     hipLaunchKernelGGL(wdot_partial_kernel, dim3(nchunk, nv), dim3(256), 0, s, Uq, Q, coll ? (const double*)Uq : Vc,
                        coll ? Q : ldv, omega_d, Q, clen, part);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(wdot_final_kernel, dim3((nv + 63) / 64), dim3(64), 0, s, part, nchunk, nv, norms2 + c0);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(kron_eval(n, mg, Egd, Vc, ldv, nv, t1, t2, Phi + (int64_t)c0 * Pts, Pts, s));
+    HIP_TRY(kron_eval(n, mg, Egd, EgTd, Vc, ldv, nv, t1, t2, Phi + (int64_t)c0 * Pts, Pts, s));
   }
   if (gscale_d) HIP_TRY(scale_rows(Phi, Pts, M, Pts, gscale_d, s));
-  std::vector<double> nrm(M), fac(M);
-  HIP_TRY(hipMemcpyAsync(nrm.data(), norms2, M * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  for (int i = 0; i < M; ++i) {
-    if (!(nrm[i] > 0) || !std::isfinite(nrm[i])) return fail(KA_ERR_SINGULAR, "an eigenfunction has zero L2 norm");
-    fac[i] = std::sqrt(lambda_host[i] / nrm[i]);
-  }
-  HIP_TRY(hipMemcpyAsync(fac_d, fac.data(), M * sizeof(double), hipMemcpyHostToDevice, s));
-  const int64_t tot = (int64_t)M * nsamples;
+  double* bad_d = up_d + obad;
+  const int64_t tot = Kp * Sp;
   hipLaunchKernelGGL(xi_scale_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, xi_dev, ldxi, M, nsamples,
-                     fac_d, XiT);
+                     Kp, Sp, up_d + olam, norms2, XiT, bad_d);
   HIP_TRY(hipGetLastError());
   const int64_t n_pt = (Pts + kFP - 1) / kFP;
-  const int n_st = (nsamples + kFS - 1) / kFS;
+  // as many sample tiles per workgroup as leave 2048 workgroups (8 on each CU,
+  // twice what is resident)
+  const int n_tiles = (int)(Sp / kFS);
+  const int tiles = (int)std::max<int64_t>(1, std::min<int64_t>(kMaxTiles, n_pt * n_tiles / 2048));
+  const int n_st = (n_tiles + tiles - 1) / tiles;
   const int64_t grid_wg = 8 * ((n_pt + 7) / 8) * (int64_t)n_st;
   if (grid_wg > ((int64_t)1 << 31) - 1) return fail(KA_ERR_ARG, "field too large for one launch");
-  hipLaunchKernelGGL(kl_field_kernel, dim3((unsigned)grid_wg), dim3(256), 0, s, Phi, Pts, Pts, XiT, nsamples, M, mu,
-                     field_dev, ldf, n_pt, n_st);
+  hipLaunchKernelGGL(kl_field_kernel, dim3((unsigned)grid_wg), dim3(256), 0, s, Phi, Pts, Pts, XiT, nsamples, Sp, M,
+                     mu, bad_d, field_dev, ldf, n_pt, n_st, tiles);
   HIP_TRY(hipGetLastError());
+  double bad = 0.0;
+  HIP_TRY(hipMemcpyAsync(&bad, bad_d, sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));   // the host vectors copied above live until here
+  if (bad != 0.0) return fail(KA_ERR_SINGULAR, "an eigenfunction has zero L2 norm");   // (no field was written)
   return KA_OK;
 }

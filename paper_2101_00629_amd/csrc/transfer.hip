@@ -175,6 +175,26 @@ __global__ void mode_product_kernel(ModeArgs a, int64_t total) {
 template <typename TIn, typename TAcc, typename TOut>
 static hipError_t launch_mode(const ModeArgs& a, hipStream_t s) {
   if (a.in_layout == LAYOUT_PT && a.out_layout == LAYOUT_PT) return launch_mode_pt<TIn, TAcc, TOut>(a, s);
+  // A dense column-major block contracted along direction 2 or 3 is a
+  // point-major one: the faster directions are its "vectors", the columns its
+  // slowest direction.  (64^3 values of 50 columns from 64 x 64 x 23: 283 us
+  // with one thread per output, 165 us like this.)
+  const int64_t dense = (int64_t)a.n_in[0] * a.n_in[1] * a.n_in[2];
+  if (a.in_layout == LAYOUT_COL && a.out_layout == LAYOUT_COL && a.mode > 0 && a.matT && !a.out_scale &&
+      a.in_ld == dense && a.out_ld == dense / a.n_in[a.mode] * a.m) {
+    const int64_t inner = a.mode == 1 ? a.n_in[0] : (int64_t)a.n_in[0] * a.n_in[1];
+    if (inner <= 0x7fffffff) {
+      ModeArgs b = a;
+      b.in_layout = b.out_layout = LAYOUT_PT;
+      b.in_ld = b.out_ld = inner;
+      b.n_in[0] = a.n_in[a.mode];
+      b.n_in[1] = a.mode == 1 ? a.n_in[2] : a.nv;
+      b.n_in[2] = a.mode == 1 ? a.nv : 1;
+      b.mode = 0;
+      b.nv = (int)inner;
+      return launch_mode_pt<TIn, TAcc, TOut>(b, s);
+    }
+  }
   int no[3] = {a.n_in[0], a.n_in[1], a.n_in[2]};
   no[a.mode] = a.m;
   const int64_t total = (int64_t)no[0] * no[1] * no[2] * a.nv;
