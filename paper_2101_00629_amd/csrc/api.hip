@@ -284,8 +284,7 @@ static int setup_impl(const ka_desc* d, hipStream_t stream, Problem** out, const
       const Mat LiT = transpose(Li);
       P->Linv[k] = upload(P, to_vec(Li), ok);
       P->LinvT[k] = upload(P, to_vec(LiT), ok);
-      P->Zinv[k] = upload(P, to_vec(matmul(LiT, Li)), ok);
-      P->ZinvT[k] = P->Zinv[k];   // the mass matrix is symmetric
+      P->ZinvT[k] = upload(P, to_vec(matmul(LiT, Li)), ok);   // symmetric
       P->Zk[k] = upload(P, to_vec(Zk), ok);   // mass matrix: exact L2 norms of eigenfunctions
       Vec xq, wq;
       element_gauss(t, d->nq > 0 ? d->nq : p + 1, xq, wq);
@@ -304,8 +303,7 @@ static int setup_impl(const ka_desc* d, hipStream_t stream, Problem** out, const
       const Mat LiT = transpose(Li);
       P->Linv[k] = upload(P, to_vec(Li), ok);
       P->LinvT[k] = upload(P, to_vec(LiT), ok);
-      P->Zinv[k] = upload(P, to_vec(matmul(LiT, Li)), ok);
-      P->ZinvT[k] = P->Zinv[k];   // the mass matrix is symmetric
+      P->ZinvT[k] = upload(P, to_vec(matmul(LiT, Li)), ok);   // symmetric
       P->Zk[k] = upload(P, to_vec(Zk), ok);   // mass matrix: exact L2 norms of eigenfunctions
       const Vec& ti = z.tint[k];
       const Vec g = greville(ti, p);
@@ -336,9 +334,7 @@ static int setup_impl(const ka_desc* d, hipStream_t stream, Problem** out, const
         free_problem(P);
         return fail(KA_ERR_SINGULAR, "collocation matrix Z_k is singular");
       }
-      P->Zinv[k] = upload(P, to_vec(Zci), ok);
       P->ZinvT[k] = upload(P, to_vec(transpose(Zci)), ok);
-      P->T[k] = upload(P, to_vec32(Rq), ok);
       P->TT[k] = upload(P, to_vec32(transpose(Rq)), ok);
       pts1d[k] = g;
       q1d[k] = xq;
@@ -450,23 +446,30 @@ static int setup_impl(const ka_desc* d, hipStream_t stream, Problem** out, const
 // ---------------------------------------------------------------------------
 // operator pieces
 // ---------------------------------------------------------------------------
-static ModeArgs mode_args(const void* in, int in_layout, int64_t in_ld, void* out, int out_layout, int64_t out_ld,
-                          const int dims[3], int mode, int m, const void* mat, const void* matT, int nv,
-                          const float* scale) {
+// a tensor block in memory: column-major with column stride ld, or point-major with point stride ld
+struct Block {
+  void* p;
+  int layout;
+  int64_t ld;
+};
+
+// direction `mode` of `in` (dims n1, n2, n3) through matT (n_mode x m): dims[mode] becomes m
+static ModeArgs mode_args(const Block& in, const Block& out, int dims[3], int mode, int m, const void* matT, int nv,
+                          const float* scale = nullptr) {
   ModeArgs a;
-  a.in = in;
-  a.in_layout = in_layout;
-  a.in_ld = in_ld;
-  a.out = out;
-  a.out_layout = out_layout;
-  a.out_ld = out_ld;
+  a.in = in.p;
+  a.in_layout = in.layout;
+  a.in_ld = in.ld;
+  a.out = out.p;
+  a.out_layout = out.layout;
+  a.out_ld = out.ld;
   for (int k = 0; k < 3; ++k) a.n_in[k] = dims[k];
   a.mode = mode;
   a.m = m;
-  a.mat = mat;
   a.matT = matT;
   a.nv = nv;
   a.out_scale = scale;
+  dims[mode] = m;
   return a;
 }
 
@@ -516,81 +519,63 @@ int gamma_step(Problem* P, const float* Y, float* Z, hipStream_t s) {
   return KA_OK;
 }
 
-// Three FP64 mode products with per-direction matrices mats[k] (n_k x n_k) on
-// a point-major block (point stride b) in `src`, through `other`; the result
-// is left in `other`.
-static int kron64_pt(Problem* P, double* const mats[3], double* const matsT[3], double* src, double* other, int nv,
-                     hipStream_t s) {
-  const int* n = P->n;
-  const int b = P->b;
-  HIP_TRY(launch_mode_f64(mode_args(src, LAYOUT_PT, b, other, LAYOUT_PT, b, n, 0, n[0], mats[0], matsT[0], nv, nullptr), s));
-  HIP_TRY(launch_mode_f64(mode_args(other, LAYOUT_PT, b, src, LAYOUT_PT, b, n, 1, n[1], mats[1], matsT[1], nv, nullptr), s));
-  HIP_TRY(launch_mode_f64(mode_args(src, LAYOUT_PT, b, other, LAYOUT_PT, b, n, 2, n[2], mats[2], matsT[2], nv, nullptr), s));
-  return KA_OK;
-}
-
-// Point-major FP64 block `src` (point stride b) -> Galerkin: J B~^-T M X ;
-// collocation: JW R_q X.  Output: point-major FP32 in w32b (point stride b).
-static int forward_transfer(Problem* P, const double* src, int nv, hipStream_t s) {
-  const int b = P->b;
-  const int* n = P->n;
-  const int* m = P->d.method == KA_GALERKIN_IBQ ? P->nt : P->nq;
-  int d0[3] = {n[0], n[1], n[2]};
-  HIP_TRY(launch_mode_f64_to_f32(mode_args(src, LAYOUT_PT, b, P->w32b, LAYOUT_PT, b, d0, 0, m[0], P->T[0], P->TT[0], nv, nullptr), s));
-  int d1[3] = {m[0], n[1], n[2]};
-  HIP_TRY(launch_mode_f32(mode_args(P->w32b, LAYOUT_PT, b, P->w32a, LAYOUT_PT, b, d1, 1, m[1], P->T[1], P->TT[1], nv, nullptr), s));
-  int d2[3] = {m[0], m[1], n[2]};
-  HIP_TRY(launch_mode_f32(mode_args(P->w32a, LAYOUT_PT, b, P->w32b, LAYOUT_PT, b, d2, 2, m[2], P->T[2], P->TT[2], nv, P->cscale), s));
-  return KA_OK;   // result in w32b
-}
-
 // Operator steps before the kernel product: X (FP64, column layout) ->
 // kernel-product input in w32b (point-major FP32, stride b).
 //   Galerkin: [L^-T if A'], then B~^-T M per direction with J on the last store
 //   (nine-step algorithm, steps 1-4).  Collocation: R_q per direction with
 //   J W on the last store (Algorithm 1, steps 1-2).
+// The first product contracts direction 1, whose fibers are contiguous in X,
+// and leaves its result point-major.
 int apply_pre(Problem* P, int form, const double* X, int64_t ldx, int nv, hipStream_t s) {
   const int b = P->b;
-  HIP_TRY(col64_to_pt64(X, ldx, P->w64a, b, P->N, nv, s));
-  double* src = P->w64a;
+  const int* m = P->d.method == KA_GALERKIN_IBQ ? P->nt : P->nq;
+  int d[3] = {P->n[0], P->n[1], P->n[2]};
+  const Block a64 = {P->w64a, LAYOUT_PT, b}, b64 = {P->w64b, LAYOUT_PT, b};
+  const Block a32 = {P->w32a, LAYOUT_PT, b}, b32 = {P->w32b, LAYOUT_PT, b};
+  Block src = {const_cast<double*>(X), LAYOUT_COL, ldx};
   if (P->d.method != KA_COLLOCATION && form == KA_APRIME) {
-    if (int rc = kron64_pt(P, P->LinvT, P->Linv, P->w64a, P->w64b, nv, s)) return rc;
-    src = P->w64b;
+    HIP_TRY(launch_mode_f64(mode_args(src, a64, d, 0, d[0], P->Linv[0], nv), s));
+    HIP_TRY(launch_mode_f64(mode_args(a64, b64, d, 1, d[1], P->Linv[1], nv), s));
+    HIP_TRY(launch_mode_f64(mode_args(b64, a64, d, 2, d[2], P->Linv[2], nv), s));
+    src = a64;
   }
-  return forward_transfer(P, src, nv, s);
+  HIP_TRY(launch_mode_f64_to_f32(mode_args(src, b32, d, 0, m[0], P->TT[0], nv), s));
+  HIP_TRY(launch_mode_f32(mode_args(b32, a32, d, 1, m[1], P->TT[1], nv), s));
+  HIP_TRY(launch_mode_f32(mode_args(a32, b32, d, 2, m[2], P->TT[2], nv, P->cscale), s));
+  return KA_OK;
 }
 
 // Operator steps after the kernel product: w32a (point-major FP32) -> Y.
 //   Galerkin: M^T B~^-1 per direction, [L^-1 if A'] (steps 7-9; step 6 is
 //   folded into the product's store).  Collocation: [Z^-1 if A'] (step 4).
+// Directions 3, 2, 1: the last product writes Y's columns along their
+// contiguous direction.
 int apply_post(Problem* P, int form, double* Y, int64_t ldy, int nv, hipStream_t s) {
   const int b = P->b;
   const int* n = P->n;
-  const int64_t N = P->N;
-  const int nn[3] = {n[0], n[1], n[2]};
+  const Block a64 = {P->w64a, LAYOUT_PT, b}, b64 = {P->w64b, LAYOUT_PT, b};
+  const Block a32 = {P->w32a, LAYOUT_PT, b}, b32 = {P->w32b, LAYOUT_PT, b};
+  const Block y = {Y, LAYOUT_COL, ldy};
+  const bool aprime = form == KA_APRIME;
   if (P->d.method != KA_COLLOCATION) {
     const int* m = P->d.method == KA_GALERKIN_IBQ ? P->nt : P->nq;
-    int d0[3] = {m[0], m[1], m[2]};
-    HIP_TRY(launch_mode_f32(mode_args(P->w32a, LAYOUT_PT, b, P->w32b, LAYOUT_PT, b, d0, 0, n[0], P->TT[0], P->T[0], nv, nullptr), s));
-    int d1[3] = {n[0], m[1], m[2]};
-    HIP_TRY(launch_mode_f32(mode_args(P->w32b, LAYOUT_PT, b, P->w32a, LAYOUT_PT, b, d1, 1, n[1], P->TT[1], P->T[1], nv, nullptr), s));
-    int d2[3] = {n[0], n[1], m[2]};
-    HIP_TRY(launch_mode_f32_to_f64(mode_args(P->w32a, LAYOUT_PT, b, P->w64b, LAYOUT_PT, b, d2, 2, n[2], P->TT[2], P->T[2], nv, nullptr), s));
-    double* res = P->w64b;
-    if (form == KA_APRIME) {
-      if (int rc = kron64_pt(P, P->Linv, P->LinvT, P->w64b, P->w64a, nv, s)) return rc;
-      res = P->w64a;
-    }
-    HIP_TRY(pt64_to_col64(res, b, Y, ldy, N, nv, s));
+    int d[3] = {m[0], m[1], m[2]};
+    HIP_TRY(launch_mode_f32(mode_args(a32, b32, d, 2, n[2], P->T[2], nv), s));
+    HIP_TRY(launch_mode_f32(mode_args(b32, a32, d, 1, n[1], P->T[1], nv), s));
+    HIP_TRY(launch_mode_f32_to_f64(mode_args(a32, aprime ? b64 : y, d, 0, n[0], P->T[0], nv), s));
+    if (!aprime) return KA_OK;
+    HIP_TRY(launch_mode_f64(mode_args(b64, a64, d, 2, n[2], P->LinvT[2], nv), s));
+    HIP_TRY(launch_mode_f64(mode_args(a64, b64, d, 1, n[1], P->LinvT[1], nv), s));
+    HIP_TRY(launch_mode_f64(mode_args(b64, y, d, 0, n[0], P->LinvT[0], nv), s));
     return KA_OK;
   }
-  if (form == KA_APRIME) {
-    HIP_TRY(launch_mode_f32in_f64(mode_args(P->w32a, LAYOUT_PT, b, P->w64a, LAYOUT_PT, b, nn, 0, n[0], P->Zinv[0], P->ZinvT[0], nv, nullptr), s));
-    HIP_TRY(launch_mode_f64(mode_args(P->w64a, LAYOUT_PT, b, P->w64b, LAYOUT_PT, b, nn, 1, n[1], P->Zinv[1], P->ZinvT[1], nv, nullptr), s));
-    HIP_TRY(launch_mode_f64(mode_args(P->w64b, LAYOUT_PT, b, P->w64a, LAYOUT_PT, b, nn, 2, n[2], P->Zinv[2], P->ZinvT[2], nv, nullptr), s));
-    HIP_TRY(pt64_to_col64(P->w64a, b, Y, ldy, N, nv, s));
+  if (aprime) {
+    int d[3] = {n[0], n[1], n[2]};
+    HIP_TRY(launch_mode_f32in_f64(mode_args(a32, a64, d, 2, n[2], P->ZinvT[2], nv), s));
+    HIP_TRY(launch_mode_f64(mode_args(a64, b64, d, 1, n[1], P->ZinvT[1], nv), s));
+    HIP_TRY(launch_mode_f64(mode_args(b64, y, d, 0, n[0], P->ZinvT[0], nv), s));
   } else {
-    HIP_TRY(cast_pt32_to_col64(P->w32a, b, Y, ldy, N, nv, P->wrow64, s));   // A itself: W(g) divided out
+    HIP_TRY(cast_pt32_to_col64(P->w32a, b, Y, ldy, P->N, nv, P->wrow64, s));   // A itself: W(g) divided out
   }
   return KA_OK;
 }
@@ -629,26 +614,24 @@ int apply_block(Problem* P, int form, const double* X, int64_t ldx, double* Y, i
 }
 
 int solve_block(Problem* P, int op, double* X, int64_t ld, int nv, hipStream_t s) {
-  double* const* mats = nullptr;
   double* const* matsT = nullptr;
   if (op == KA_ZINV) {
     if (P->wrow64) HIP_TRY(scale_rows(X, P->N, nv, ld, P->wrow64, s));   // general NURBS: diag(W(g)) first
-    mats = P->Zinv;
     matsT = P->ZinvT;
   } else if (P->d.method == KA_COLLOCATION) {
     return fail(KA_ERR_STATE, "L solves exist for the Galerkin methods only");
   } else if (op == KA_LINV) {
-    mats = P->Linv;
     matsT = P->LinvT;
   } else if (op == KA_LTINV) {
-    mats = P->LinvT;
     matsT = P->Linv;
   } else {
     return fail(KA_ERR_ARG, "bad solve op");
   }
-  HIP_TRY(col64_to_pt64(X, ld, P->w64a, P->b, P->N, nv, s));
-  if (int rc = kron64_pt(P, mats, matsT, P->w64a, P->w64b, nv, s)) return rc;
-  HIP_TRY(pt64_to_col64(P->w64b, P->b, X, ld, P->N, nv, s));
+  int d[3] = {P->n[0], P->n[1], P->n[2]};
+  const Block x = {X, LAYOUT_COL, ld}, a = {P->w64a, LAYOUT_COL, P->N}, b = {P->w64b, LAYOUT_COL, P->N};
+  HIP_TRY(launch_mode_f64(mode_args(x, a, d, 0, d[0], matsT[0], nv), s));
+  HIP_TRY(launch_mode_f64(mode_args(a, b, d, 1, d[1], matsT[1], nv), s));
+  HIP_TRY(launch_mode_f64(mode_args(b, x, d, 2, d[2], matsT[2], nv), s));
   return KA_OK;
 }
 

@@ -214,7 +214,7 @@ struct KlArena {
 };
 
 ModeArgs col_mode(const double* in, int64_t in_ld, double* out, int64_t out_ld, const int dims[3], int mode, int m,
-                  const double* mat, const double* matT, int nv) {
+                  const double* matT, int nv) {
   ModeArgs a;
   a.in = in;
   a.in_layout = LAYOUT_COL;
@@ -225,27 +225,24 @@ ModeArgs col_mode(const double* in, int64_t in_ld, double* out, int64_t out_ld, 
   for (int k = 0; k < 3; ++k) a.n_in[k] = dims[k];
   a.mode = mode;
   a.m = m;
-  a.mat = mat;
   a.matT = matT;
   a.nv = nv;
   a.out_scale = nullptr;
   return a;
 }
 
-// (E_3 x E_2 x E_1) V[:, 0 : nv] -> out (column-major, ld = m0 m1 m2); ET: the transposes
-hipError_t kron_eval(const int n[3], const int m[3], double* const E[3], double* const ET[3], const double* V,
-                     int64_t ldv, int nv, double* t1, double* t2, double* out, int64_t ld_out, hipStream_t s) {
+// (E_3 x E_2 x E_1) V[:, 0 : nv] -> out (column-major, ld = m0 m1 m2), from the transposes of E_k
+hipError_t kron_eval(const int n[3], const int m[3], double* const ET[3], const double* V, int64_t ldv,
+                     int nv, double* t1, double* t2, double* out, int64_t ld_out, hipStream_t s) {
   const int d0[3] = {n[0], n[1], n[2]};
   const int d1[3] = {m[0], n[1], n[2]};
   const int d2[3] = {m[0], m[1], n[2]};
   const int64_t l1 = (int64_t)m[0] * n[1] * n[2], l2 = (int64_t)m[0] * m[1] * n[2];
-  hipError_t e = launch_mode_f64(col_mode(V, ldv, t1, l1, d0, 0, m[0], E[0], ET[0], nv), s);
-  if (e == hipSuccess) e = launch_mode_f64(col_mode(t1, l1, t2, l2, d1, 1, m[1], E[1], ET[1], nv), s);
-  if (e == hipSuccess) e = launch_mode_f64(col_mode(t2, l2, out, ld_out, d2, 2, m[2], E[2], ET[2], nv), s);
+  hipError_t e = launch_mode_f64(col_mode(V, ldv, t1, l1, d0, 0, m[0], ET[0], nv), s);
+  if (e == hipSuccess) e = launch_mode_f64(col_mode(t1, l1, t2, l2, d1, 1, m[1], ET[1], nv), s);
+  if (e == hipSuccess) e = launch_mode_f64(col_mode(t2, l2, out, ld_out, d2, 2, m[2], ET[2], nv), s);
   return e;
 }
-
-std::vector<double> to_rows(const Mat& A) { return A.a; }
 
 }  // namespace
 
@@ -361,15 +358,14 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
   };
   if (coll && !P->kl_omega) {
     for (int k = 0; k < 3; ++k) {
-      P->kl_Eq[k] = keep(to_rows(Eq[k]));
-      P->kl_EqT[k] = P->kl_Eq[k] ? keep(to_rows(transpose(Eq[k]))) : nullptr;
+      P->kl_EqT[k] = keep(transpose(Eq[k]).a);
       if (!P->kl_EqT[k]) return fail(KA_ERR_OOM, "device allocation failed in ka_kl_sample");
       P->kl_mq[k] = mq[k];
     }
     P->kl_omega = keep(omega);
     if (!P->kl_omega) return fail(KA_ERR_OOM, "device allocation failed in ka_kl_sample");
   }
-  // this call's workspace; the host's data (grid matrices and transposes,
+  // this call's workspace; the host's data (transposed grid matrices,
   // eigenvalues, the cleared flag) go up in one copy
   const int chunk = std::min(M, 128);
   const int64_t tq = std::max((int64_t)mq[0] * n[1] * n[2], (int64_t)mq[0] * mq[1] * n[2]);
@@ -379,11 +375,9 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
   const int Kp = (M + 3) / 4 * 4;
   const int64_t Sp = ((int64_t)nsamples + kFS - 1) / kFS * kFS;
   std::vector<double> up;
-  size_t oE[3], oET[3];
+  size_t oET[3];
   for (int k = 0; k < 3; ++k) {
     const Mat ET = transpose(Eg[k]);
-    oE[k] = up.size();
-    up.insert(up.end(), Eg[k].a.begin(), Eg[k].a.end());
     oET[k] = up.size();
     up.insert(up.end(), ET.a.begin(), ET.a.end());
   }
@@ -413,11 +407,9 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
   auto at = [&](size_t i) { return (double*)((char*)P->kl_buf + ar.off[i]); };
   double* up_d = at(iup);
   HIP_TRY(hipMemcpyAsync(up_d, up.data(), up.size() * sizeof(double), hipMemcpyHostToDevice, s));
-  double *Eqd[3], *EqTd[3], *Egd[3], *EgTd[3];
+  double *EqTd[3], *EgTd[3];
   for (int k = 0; k < 3; ++k) {
-    Eqd[k] = coll ? P->kl_Eq[k] : P->Zk[k];    // Galerkin: Z v with the mass matrices (symmetric)
-    EqTd[k] = coll ? P->kl_EqT[k] : P->Zk[k];
-    Egd[k] = up_d + oE[k];
+    EqTd[k] = coll ? P->kl_EqT[k] : P->Zk[k];    // Galerkin: Z v with the mass matrices (symmetric)
     EgTd[k] = up_d + oET[k];
   }
   double* t1 = at(it1);
@@ -435,13 +427,13 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
     const int nv = std::min(chunk, M - c0);
     const double* Vc = V_dev + (int64_t)c0 * ldv;
     // collocation: phi at the Gauss points, norms^2 = sum omega phi^2; Galerkin: Z v, norms^2 = v^T Z v
-    HIP_TRY(kron_eval(n, mq, Eqd, EqTd, Vc, ldv, nv, t1, t2, Uq, Q, s));
+    HIP_TRY(kron_eval(n, mq, EqTd, Vc, ldv, nv, t1, t2, Uq, Q, s));
     hipLaunchKernelGGL(wdot_partial_kernel, dim3(nchunk, nv), dim3(256), 0, s, Uq, Q, coll ? (const double*)Uq : Vc,
                        coll ? Q : ldv, omega_d, Q, clen, part);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(wdot_final_kernel, dim3((nv + 63) / 64), dim3(64), 0, s, part, nchunk, nv, norms2 + c0);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(kron_eval(n, mg, Egd, EgTd, Vc, ldv, nv, t1, t2, Phi + (int64_t)c0 * Pts, Pts, s));
+    HIP_TRY(kron_eval(n, mg, EgTd, Vc, ldv, nv, t1, t2, Phi + (int64_t)c0 * Pts, Pts, s));
   }
   if (gscale_d) HIP_TRY(scale_rows(Phi, Pts, M, Pts, gscale_d, s));
   double* bad_d = up_d + obad;
