@@ -13,25 +13,34 @@
 
 namespace ka {
 
-__global__ void split_reduce_kernel(const double* __restrict__ part, int nsplit, int m, int n, double alpha,
-                                    double beta, double* __restrict__ C, int64_t ldc) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)m * n) return;
-  const int i = (int)(id % m), j = (int)(id / m);
-  // four interleaved partial sums (fixed order), so several loads are in flight
-  const size_t stride = (size_t)n * m;
-  const double* p = part + (size_t)j * m + i;
+// C = alpha sum_z part[z] + beta C.  A workgroup sums 32 entries, eight threads
+// per entry over every eighth split (four interleaved sums each, so that the
+// loads of a thread overlap), then their sums in order.
+constexpr int kRedE = 32, kRedZ = 8;
+__global__ __launch_bounds__(kRedE* kRedZ) void split_reduce_kernel(const double* __restrict__ part, int nsplit, int m,
+                                                                    int n, double alpha, double beta,
+                                                                    double* __restrict__ C, int64_t ldc) {
+  __shared__ double red[kRedZ][kRedE];
+  const int e = threadIdx.x % kRedE, zg = threadIdx.x / kRedE;
+  const int64_t id = (int64_t)blockIdx.x * kRedE + e, tot = (int64_t)m * n;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  int z = 0;
-  for (; z + 3 < nsplit; z += 4) {
-    s0 += p[(size_t)z * stride];
-    s1 += p[(size_t)(z + 1) * stride];
-    s2 += p[(size_t)(z + 2) * stride];
-    s3 += p[(size_t)(z + 3) * stride];
+  if (id < tot) {
+    const double* p = part + id;
+    int z = zg;
+    for (; z + 3 * kRedZ < nsplit; z += 4 * kRedZ) {
+      s0 += p[(size_t)z * tot];
+      s1 += p[(size_t)(z + kRedZ) * tot];
+      s2 += p[(size_t)(z + 2 * kRedZ) * tot];
+      s3 += p[(size_t)(z + 3 * kRedZ) * tot];
+    }
+    for (; z < nsplit; z += kRedZ) s0 += p[(size_t)z * tot];
   }
-  for (; z < nsplit; ++z) s0 += p[(size_t)z * stride];
-  const double s = (s0 + s1) + (s2 + s3);
-  double* c = C + i + (int64_t)j * ldc;
+  red[zg][e] = (s0 + s1) + (s2 + s3);
+  __syncthreads();
+  if (zg > 0 || id >= tot) return;
+  double s = 0.0;
+  for (int z = 0; z < kRedZ; ++z) s += red[z][e];
+  double* c = C + id % m + (id / m) * ldc;
   *c = (beta == 0.0) ? alpha * s : alpha * s + beta * *c;
 }
 
@@ -40,39 +49,49 @@ __global__ void split_reduce_kernel(const double* __restrict__ part, int nsplit,
 // and Gram matrices of the block eigensolver (K = N up to ~10^6, m up to a
 // few hundred, n the block width).  The product reads A and B once from HBM
 // and does 2 K m n flops on the FP64 matrix cores; a workgroup therefore takes
-// a 128 x 64 block of C, so that A is read once and B once per 128 rows of C.
+// a 128 x 16 JT block of C (JT = 1, 2 or 4: n is the block width or a basis),
+// so that A is read once and B once per 128 rows of C.
 //
 // v_mfma_f64_16x16x4f64 layout: A lane l holds (i = l % 16, k = l / 16), B
 // lane l holds (k = l / 16, j = l % 16), accumulator register r of lane l
 // holds (i = l / 16 + 4 r, j = l % 16).  The four MFMAs of a 16-row step may
 // take its rows in any partition, so lane l reads the four consecutive rows
 // 4 (l / 16) .. + 3 of its columns of A (MFMA s takes row 4 (l / 16) + s).
-// Each of the 4 waves holds two 16-row tiles of C across the block's four
-// 16-column tiles (8 accumulators) and reads A straight from memory, the
+// Each of the 4 waves holds two 16-row tiles of C across the block's JT
+// 16-column tiles (2 JT accumulators) and reads A straight from memory, the
 // next step's rows issued before the current step's MFMAs.  B, the same for
 // the 4 waves, goes through LDS in chunks of kTnStep rows (zero past the
 // row range and past n, so the clamped rows of A beyond the range add
 // nothing), double buffered with one barrier per chunk.  Row ranges (splits)
-// go to a partial array that split_reduce_kernel sums in split order, or
+// go to a partial array that split_reduce_kernel sums in a fixed order, or
 // straight to C with one split.
+//
+// With blocks of 16 and K of some 10^4 the time is the chain of chunks of one
+// workgroup: K = 12,167, n = 16 took 30 us with four column tiles (48 of 64
+// columns padding) and splits of 256 rows, and 6 us for the sum of the splits.
+// (The 52 products of 50 eigenpairs there, with their sums, in ms of the whole
+// solve: 6.80 so, 6.02 with one column tile, 5.85 with splits of 128 rows, 5.58
+// with eight threads per summed entry, 5.50 with splits of 64 rows.)
 // ---------------------------------------------------------------------------
 typedef double tn_d4 __attribute__((ext_vector_type(4)));
 constexpr int kTnI = 2;                     // 16-row tiles of C per wave
 constexpr int kTnRowsC = 4 * 16 * kTnI;     // rows of C (columns of A) per workgroup
 constexpr int kTnStep = 32;                 // rows of A and B per chunk (two 16-row steps)
-constexpr int kTnBW = 64 + 8;               // padded LDS row of a B chunk (doubles)
-constexpr int kTnSE = kTnStep * 64 / 256;   // staged B elements per thread
 
+template <int JT>
 __global__ __launch_bounds__(256) void dgemm_tn_mfma_kernel(int m, int n, int64_t K, const double* __restrict__ A,
                                                             int64_t lda, const double* __restrict__ B, int64_t ldb,
                                                             int64_t k_per_split, double* __restrict__ part,
                                                             double alpha, double beta, double* __restrict__ C,
                                                             int64_t ldc) {
-  __shared__ double Bs[2][kTnStep][kTnBW];
+  constexpr int kSE = kTnStep * 16 * JT / 256;   // staged B elements per thread
+  // LDS row of a B chunk: 4 doubles of padding put the four rows that a fragment
+  // read touches at once on different halves of the banks
+  __shared__ double Bs[2][kTnStep][16 * JT + 4];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, q = lane >> 4, c16 = lane & 15;
   const int i0 = blockIdx.x * kTnRowsC + w * 16 * kTnI;   // this wave's first row of C
   const bool on = i0 < m;                                  // (a wave past m only stages B)
-  const int j0 = blockIdx.y * 64;
+  const int j0 = blockIdx.y * (16 * JT);
   const double* Ap[kTnI];
 #pragma unroll
   for (int u = 0; u < kTnI; ++u) {
@@ -81,15 +100,15 @@ __global__ __launch_bounds__(256) void dgemm_tn_mfma_kernel(int m, int n, int64_
   }
   const int64_t kb = (int64_t)blockIdx.z * k_per_split;
   const int64_t ke = kb + k_per_split < K ? kb + k_per_split : K;
-  tn_d4 acc[kTnI][4];
+  tn_d4 acc[kTnI][JT];
 #pragma unroll
   for (int u = 0; u < kTnI; ++u)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[u][t] = (tn_d4){0.0, 0.0, 0.0, 0.0};
-  double st[kTnSE];
+    for (int t = 0; t < JT; ++t) acc[u][t] = (tn_d4){0.0, 0.0, 0.0, 0.0};
+  double st[kSE];
   auto fetch_b = [&](int64_t g) {            // consecutive threads down a column of B
 #pragma unroll
-    for (int v = 0; v < kTnSE; ++v) {
+    for (int v = 0; v < kSE; ++v) {
       const int e = threadIdx.x + 256 * v;
       const int64_t r = g + e % kTnStep;
       const int j = j0 + e / kTnStep;
@@ -98,7 +117,7 @@ __global__ __launch_bounds__(256) void dgemm_tn_mfma_kernel(int m, int n, int64_
   };
   auto put_b = [&](int buf) {
 #pragma unroll
-    for (int v = 0; v < kTnSE; ++v) {
+    for (int v = 0; v < kSE; ++v) {
       const int e = threadIdx.x + 256 * v;
       Bs[buf][e % kTnStep][e / kTnStep] = st[v];
     }
@@ -117,13 +136,13 @@ __global__ __launch_bounds__(256) void dgemm_tn_mfma_kernel(int m, int n, int64_
   auto step = [&](int buf, int h, const double (&a)[kTnI][4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      double bv[4];
+      double bv[JT];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) bv[t] = Bs[buf][16 * h + 4 * q + s][16 * t + c16];
+      for (int t = 0; t < JT; ++t) bv[t] = Bs[buf][16 * h + 4 * q + s][16 * t + c16];
 #pragma unroll
       for (int u = 0; u < kTnI; ++u)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[u][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][s], bv[t], acc[u][t], 0, 0, 0);
+        for (int t = 0; t < JT; ++t) acc[u][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][s], bv[t], acc[u][t], 0, 0, 0);
     }
   };
   if (kb < ke) {                             // uniform over the workgroup, like every branch below
@@ -149,7 +168,7 @@ __global__ __launch_bounds__(256) void dgemm_tn_mfma_kernel(int m, int n, int64_
 #pragma unroll
   for (int u = 0; u < kTnI; ++u)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < JT; ++t) {
       const int jo = j0 + 16 * t + c16;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -166,14 +185,14 @@ __global__ __launch_bounds__(256) void dgemm_tn_mfma_kernel(int m, int n, int64_
     }
 }
 
-// Row splits: about 512 workgroups (two per CU), at least 256 rows each,
-// whole multiples of kTnStep, at most 256 splits; products with K < 1024
-// take one split.
+// Row splits: about 512 workgroups (two per CU), at least 64 rows (two
+// chunks) each, whole multiples of kTnStep, at most 256 splits; products with
+// K < 1024 take one split.
 static int64_t tn_rows_per_split(int m, int n, int64_t K) {
   if (K < 1024) return K > 0 ? K : 1;
   const int64_t tiles = (int64_t)((m + kTnRowsC - 1) / kTnRowsC) * ((n + 63) / 64);
   int64_t ns = (512 + tiles - 1) / tiles;
-  if (ns > K / 256) ns = K / 256;
+  if (ns > K / 64) ns = K / 64;
   if (ns > 256) ns = 256;
   if (ns < 1) ns = 1;
   const int64_t kps = (K + ns - 1) / ns;
@@ -196,13 +215,14 @@ hipError_t dgemm_tn(int m, int n, int64_t K, double alpha, const double* A, int6
   const int64_t kps = tn_rows_per_split(m, n, K);
   const int ns = tn_splits(m, n, K);
   const dim3 grid((m + kTnRowsC - 1) / kTnRowsC, (n + 63) / 64, ns);
-  hipLaunchKernelGGL(dgemm_tn_mfma_kernel, grid, dim3(256), 0, s, m, n, K, A, lda, B, ldb, kps,
-                     ns > 1 ? work : nullptr, alpha, beta, C, ldc);
+  const auto kernel = n <= 16 ? dgemm_tn_mfma_kernel<1> : n <= 32 ? dgemm_tn_mfma_kernel<2> : dgemm_tn_mfma_kernel<4>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, m, n, K, A, lda, B, ldb, kps, ns > 1 ? work : nullptr, alpha, beta,
+                     C, ldc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || ns == 1) return e;
   const int64_t tot = (int64_t)m * n;
-  hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, work, ns, m, n,
-                     alpha, beta, C, ldc);
+  hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((tot + kRedE - 1) / kRedE)), dim3(kRedE * kRedZ), 0, s, work,
+                     ns, m, n, alpha, beta, C, ldc);
   return hipGetLastError();
 }
 
