@@ -882,6 +882,7 @@ static int rows_per_block(int b, int precision) {
 
 constexpr int64_t kMinSplitCols = 512;
 constexpr double kF16MinWork = 4e8;
+constexpr int64_t kFineTarget = 512;
 
 GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
   GammaPlan p;
@@ -897,6 +898,9 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
     p.work_bytes = 0;
     p.stated_bytes = 0;
     p.f16 = false;
+    p.fine_nsplit = 0;
+    p.fine_cols = 0;
+    p.fine_partial_bytes = 0;
     return p;
   }
   // Fill the chip: aim for >= 2048 workgroups, but keep >= kMinSplitCols
@@ -925,13 +929,17 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
   // of the XCD count: the grouped grid then keeps every split on one XCD, so
   // its column range is fetched from HBM into that XCD's L2 once.
   if (ns >= kXcds) ns = (ns + kXcds - 1) / kXcds * kXcds;
-  // The split-FP16 product (gamma_f16x3.hip) pays for its pre-pass from
+  // The split-FP16 product (gamma_f16x3.hip) pays for its pre-pass from about
   // kF16MinWork pairs times vectors on.  Measured on square products (us, FP32
-  // against split FP16): b = 16, 3,375 points 30.8 / 29.9 Gaussian, 4,913 points
-  // 33.2 / 35.3 exponential, 8,000 points 43.2 / 35.5; b = 32, 3,375 points 47.2
-  // / 32.9; b = 64, 3,375 points 35.9 / 29.6.  A product with b = 16 whose
-  // columns are not split has had no scratch, which its callers rely on, and
-  // keeps the FP32 matrix cores (524,288 rows and more, or under 1,024 columns).
+  // with the fine splits below / split FP16): b = 16, 4,913 points (3.9e8) 25.3 /
+  // 35.2 exponential, 27.4 / 30.8 Gaussian, 6,500 points (6.8e8) 32.7 / 40.7 and
+  // 34.0 / 34.7, 8,000 points (1.0e9) 40.4 / 41.4 and 40.4 / 35.3; b = 32, 3,375
+  // points (3.6e8) 23.4 / 38.4 exponential, 4,913 points (7.7e8) 38.4 / 39.6 and
+  // 49.0 / 35.4; b = 64, 2,028 points (2.6e8) 14.2 / 33.6 exponential, 3,375
+  // points (7.3e8) 29.8 / 33.2, 4,913 points (1.5e9) 56.2 / 44.7.  A product with
+  // b = 16 whose columns are not split has had no scratch, which its callers rely
+  // on, and keeps the FP32 matrix cores (524,288 rows and more, or under 1,024
+  // columns).
   const bool f16 = (b != 16 || ns > 1) && (double)nr * nc * b >= kF16MinWork;
   // Whole tile groups per split: only the last split can end in a padding tile.
   int64_t cps = (nc + ns - 1) / ns;
@@ -943,11 +951,33 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
   p.cols_per_split = cps;
   p.partial_bytes = ns > 1 ? (size_t)ns * nr * b * sizeof(float) : 0;
   p.ysplit_bytes = precision == KA_BF16X3 ? (size_t)((nc + kCT - 1) / kCT) * kCT * b * 4 : 0;
+  // Small products leave most CUs idle, and their time is one workgroup's
+  // columns: while the splits above make fewer than kFineTarget workgroups, and
+  // where the scratch holds the partial sums, finer ones of 64 columns (one
+  // tile) or a multiple of a flush group.  Measured on square products (us,
+  // 512-column splits against these): b = 16, 343 points 17.1 / 11.2, 1,000
+  // points 38.8 / 11.1, 2,028 points 33.0 / 11.8, 3,366 points 29.8 / 18.4,
+  // 4,913 points 31.9 / 25.3; b = 64, 1,000 points 46.4 / 13.6.
+  p.fine_nsplit = 0;
+  p.fine_cols = 0;
+  p.fine_partial_bytes = 0;
+  if (!f16 && p.row_blocks * p.nsplit < kFineTarget) {
+    const int64_t want = nc / ((kFineTarget + p.row_blocks - 1) / p.row_blocks);
+    const int64_t group = kFlushTiles * kCT;
+    const int64_t fc = want <= kCT ? kCT : (want + group - 1) / group * group;
+    const int64_t nf = (nc + fc - 1) / fc;
+    if (nf > p.nsplit) {
+      p.fine_nsplit = (int)nf;
+      p.fine_cols = fc;
+      p.fine_partial_bytes = (size_t)nf * nr * b * sizeof(float);
+    }
+  }
   const size_t part = (p.partial_bytes + 255) / 256 * 256;
-  const size_t fast = part + (f16 ? (gamma_f16x3_bytes(nc, b) + 255) / 256 * 256 : 0);
+  const size_t fast = p.fine_nsplit > 0 ? (p.fine_partial_bytes + 255) / 256 * 256
+                                        : part + (f16 ? (gamma_f16x3_bytes(nc, b) + 255) / 256 * 256 : 0);
   p.f16 = f16 && precision == KA_FP32;
   p.base_bytes = part + p.ysplit_bytes;
-  p.work_bytes = p.f16 ? fast : p.base_bytes;
+  p.work_bytes = p.f16 ? fast : (p.fine_nsplit > 0 ? fast : part) + p.ysplit_bytes;
   p.stated_bytes = fast + p.ysplit_bytes;
   p.xcd_splits = ns_grid >= kXcds ? (int)ns_grid : 0;
   return p;
@@ -994,7 +1024,13 @@ static hipError_t launch_kernel_variant(const GammaLaunch& a, int b, int precisi
 
 hipError_t launch_gamma(GammaLaunch a, size_t work_bytes, int kernel, int b, int precision, hipStream_t s) {
   if (a.nr <= 0) return hipSuccess;
-  const GammaPlan p = gamma_plan(a.nr, a.nc, b, precision);
+  GammaPlan p = gamma_plan(a.nr, a.nc, b, precision);
+  if (p.fine_nsplit > 0 && work_bytes >= p.work_bytes) {
+    p.nsplit = p.fine_nsplit;
+    p.cols_per_split = p.fine_cols;
+    p.partial_bytes = p.fine_partial_bytes;
+    p.xcd_splits = 0;
+  }
   a.nsplit = p.nsplit;
   a.cols_per_split = p.cols_per_split;
   a.row_blocks = p.row_blocks;

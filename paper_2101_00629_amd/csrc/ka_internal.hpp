@@ -49,6 +49,9 @@ struct GammaPlan {
   size_t stated_bytes;    // ka_gamma_workspace: enough for it at either precision
   bool f16;               // FP32: contraction on the FP16 matrix cores where the scratch holds work_bytes
   int xcd_splits;         // 0, or the split count rounded up to the XCD count (grouped grid)
+  int fine_nsplit;        // 0, or the splits to take where the scratch holds work_bytes
+  int64_t fine_cols;
+  size_t fine_partial_bytes;
 };
 
 GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision);
