@@ -356,9 +356,14 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
       for (int k = 0; k < 3; ++k) t -= (2.0 * p.h[k] + p.l[k]) * (double)p.l[k];
       Sr[rb] = (float)exp2(t);
     } else {
-      rx[rb] = centred(a, xr[0], c0);
-      ry[rb] = centred(a, xr[1], c1);
-      rz[rb] = centred(a, xr[2], c2);
+      // (a row at infinity stays there: Gamma = 0)
+      auto row = [&](float x, float c) {
+        const float t = centred(a, x, c);
+        return finite_bits(t) ? t : x * a.coord_scale;
+      };
+      rx[rb] = row(xr[0], c0);
+      ry[rb] = row(xr[1], c1);
+      rz[rb] = row(xr[2], c2);
       Sr[rb] = 1.f;
     }
   }
@@ -679,6 +684,9 @@ void gamma_f16x3_kernel(GammaLaunch a) {
   launch_centre(a, cl);
   float c0, c1, c2;
   (void)gram_rows<RB>(a, rblk, s_box, c0, c1, c2);
+  c0 = finite_bits(c0) ? c0 : 0.f;   // (rows at infinity)
+  c1 = finite_bits(c1) ? c1 : 0.f;
+  c2 = finite_bits(c2) ? c2 : 0.f;
   // the rows' points relative to the launch's centre, whether they are on the
   // lattice, and the flags of the columns' groups
   int flags = 0;
