@@ -59,7 +59,8 @@ enum ka_precision { KA_FP32 = 0,  /* FP32 kernel tiles, FP32 MFMA contraction; l
                                      products contract pairs of FP16 parts that hold
                                      FP32's significand (3 FP16 MFMAs, FP32 accumulation) */
                     KA_BF16X3 = 1 /* FP32 tiles split hi+lo into BF16, 3 BF16 MFMAs,
-                                     FP32 accumulation                               */ };
+                                     FP32 accumulation; large Gaussian products as
+                                     KA_FP32, which is faster there                  */ };
 enum ka_form { KA_A = 0,          /* the covariance matrix A itself                  */
                KA_APRIME = 1      /* the standard-form operator A' (Sec. 3, eq. standard):
                                      Galerkin L^-1 A L^-T, collocation Z^-1 A         */ };
@@ -247,9 +248,11 @@ int ka_eigs(ka_problem* p, int M, double tol, int maxit, double* lambda_host, in
  * precision KA_FP32 or KA_BF16X3.  Scratch from `work_dev` (work_bytes,
  * 16-byte aligned): the split-K partial sums (nsplit * nr * b * 4 bytes when
  * the columns are split) and, for KA_BF16X3, Y split into hi/lo BF16 parts
- * (ceil(nc / 64) * 64 * b * 4 bytes).  Large KA_FP32 products also split Y and
- * the points into FP16 parts (about (4 b + 64) nc bytes) and then run 1.5 to 3
- * times as fast; with less scratch than that they run on the FP32 matrix cores.
+ * (ceil(nc / 64) * 64 * b * 4 bytes).  Large KA_FP32 products (and Gaussian
+ * KA_BF16X3 ones) split Y and the points into FP16 parts (about (4 b + 64) nc
+ * bytes) and then run 1.5 to 3 times as fast; small products split their columns
+ * further, with more partial sums.  With less scratch than that they run on the
+ * FP32 (or BF16) matrix cores in coarser splits.
  * Pass ka_gamma_workspace() bytes.  Async on `stream`. */
 int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, int64_t nr,
                    const float* xc_dev, int64_t nc, const float* Y_dev, int b, float* Z_dev,

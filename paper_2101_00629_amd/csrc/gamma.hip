@@ -975,9 +975,9 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
   const size_t part = (p.partial_bytes + 255) / 256 * 256;
   const size_t fast = p.fine_nsplit > 0 ? (p.fine_partial_bytes + 255) / 256 * 256
                                         : part + (f16 ? (gamma_f16x3_bytes(nc, b) + 255) / 256 * 256 : 0);
-  p.f16 = f16 && precision == KA_FP32;
+  p.f16 = f16;
   p.base_bytes = part + p.ysplit_bytes;
-  p.work_bytes = p.f16 ? fast : (p.fine_nsplit > 0 ? fast : part) + p.ysplit_bytes;
+  p.work_bytes = f16 ? std::max(fast, p.base_bytes) : (p.fine_nsplit > 0 ? fast : part) + p.ysplit_bytes;
   p.stated_bytes = fast + p.ysplit_bytes;
   p.xcd_splits = ns_grid >= kXcds ? (int)ns_grid : 0;
   return p;
@@ -1038,7 +1038,13 @@ hipError_t launch_gamma(GammaLaunch a, size_t work_bytes, int kernel, int b, int
   if (a.nc <= 0) {
     return fill_zero_f32(a.Z, a.nr * b, s);
   }
-  if (precision == KA_BF16X3) {
+  // The Gaussian product in split BF16 is slower than in split FP16, which forms
+  // its exponents on the matrix cores too, and less accurate (70,520 points: b =
+  // 16 1201 / 991 us, b = 32 1381 / 1251 us; 287,496 points, b = 64 34.6 / 33.0
+  // ms; relative error 4e-6 / 2e-7); the exponential one is not (b = 32 1625 /
+  // 1775 us).
+  const bool f16 = p.f16 && work_bytes >= p.work_bytes && (precision == KA_FP32 || kernel == KA_GAUSSIAN);
+  if (precision == KA_BF16X3 && !f16) {
     a.ys = gamma_ysplit_ptr(a.partial, p);
     if (!a.ys) return hipErrorInvalidValue;
     const hipError_t e = launch_split(a.Y, a.nc, a.ys, b, s);
@@ -1047,7 +1053,7 @@ hipError_t launch_gamma(GammaLaunch a, size_t work_bytes, int kernel, int b, int
   const dim3 grid = p.xcd_splits > 0 ? dim3((unsigned)(p.row_blocks * p.xcd_splits), 1u)
                                      : dim3((unsigned)p.row_blocks, (unsigned)p.nsplit);
   hipError_t e;
-  if (p.f16 && work_bytes >= p.work_bytes) {
+  if (f16) {
     gamma_f16x3_place(a, b, (char*)a.partial + (p.partial_bytes + 255) / 256 * 256);
     e = launch_gamma_f16x3(a, kernel, b, grid, s);
   } else {

@@ -47,7 +47,7 @@ struct GammaPlan {
   size_t base_bytes;      // least scratch: partials (256-byte aligned), then the pre-split Y
   size_t work_bytes;      // scratch of the fastest path at this precision (base_bytes or more)
   size_t stated_bytes;    // ka_gamma_workspace: enough for it at either precision
-  bool f16;               // FP32: contraction on the FP16 matrix cores where the scratch holds work_bytes
+  bool f16;               // contraction on the FP16 matrix cores where the scratch holds work_bytes
   int xcd_splits;         // 0, or the split count rounded up to the XCD count (grouped grid)
   int fine_nsplit;        // 0, or the splits to take where the scratch holds work_bytes
   int64_t fine_cols;
