@@ -354,63 +354,64 @@ hipError_t dgemm_nn(int64_t M, int n, int k, double alpha, const double* A, int6
 // ---------------------------------------------------------------------------
 // Cholesky of a small SPD Gram matrix G = R^T R and R^-1 (upper), n <= 64.
 // status: 0 ok, 1 a pivot was not positive or lost (rank-deficient block).
+//
+// One workgroup; the time is the chain of its 2 n steps.  Each step divides
+// row j (column i of R^-1, which is solved for from the last row up) by its
+// pivot and takes its outer product off what is left, an entry per thread and
+// one barrier: n = 16 takes 15 us, 21 us with one thread per row and a chain of
+// n sums per step.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void chol_upper_inv_kernel(const double* __restrict__ G, int n, int ldg,
-                                                            double* __restrict__ Rinv, int ldr, int* status,
-                                                            const double* __restrict__ ref) {
-  __shared__ double R[64][65];
-  __shared__ double X[64][65];
-  __shared__ int bad;
-  __shared__ double piv;
-  const int t = threadIdx.x;
-  if (t == 0) bad = 0;
-  for (int i = 0; i < n; ++i) R[i][t] = (t < n) ? G[i + t * ldg] : 0.0;   // R holds G (symmetric)
-  __syncthreads();
-  for (int j = 0; j < n; ++j) {
-    // row j of R: R[j][j] = sqrt(G_jj - sum_k R_kj^2), R[j][i] = (G_ji - sum_k R_kj R_ki) / R_jj
-    if (t == 0) {
-      double d = R[j][j];
-      for (int k = 0; k < j; ++k) d -= R[k][j] * R[k][j];
-      const double orig = G[j + j * ldg];
-      const double floor = ref ? kOrthKeep * kOrthKeep * ref[j] * ref[j] : 0.0;
-      if (!(d > 1e-26 * orig) || !(orig > 1e-300) || !(d > floor)) {
-        bad = 1;
-        d = 1.0;
+constexpr int kCholThreads = 256;
+__global__ __launch_bounds__(kCholThreads) void chol_upper_inv_kernel(const double* __restrict__ G, int n, int ldg,
+                                                                      double* __restrict__ Rinv, int ldr,
+                                                                      int* status, const double* __restrict__ ref) {
+  __shared__ double R[64][65];   // upper triangle: G, then R
+  __shared__ double X[64][65];   // X[c][i]: entry (i, c) of R^-1
+  __shared__ double orig[64], low[64], rd[64];
+  const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+  for (int i = r0; i < n; i += kCholThreads / 64)
+    if (c < n) {
+      R[i][c] = G[i + c * ldg];
+      X[c][i] = i == c ? 1.0 : 0.0;
+      if (i == c) {
+        orig[i] = G[i + i * ldg];
+        low[i] = ref ? kOrthKeep * kOrthKeep * ref[i] * ref[i] : 0.0;
       }
-      piv = sqrt(d);
     }
-    __syncthreads();
-    if (t > j && t < n) {
-      double sv = R[j][t];
-      for (int k = 0; k < j; ++k) sv -= R[k][j] * R[k][t];
-      R[j][t] = sv / piv;
+  __syncthreads();
+  int bad = 0;
+  for (int j = 0; j < n; ++j) {   // R[j][j] = sqrt(G_jj - sum_k R_kj^2), R[j][c] = (G_jc - sum_k R_kj R_kc) / R_jj
+    double d = R[j][j];
+    if (!(d > 1e-26 * orig[j]) || !(orig[j] > 1e-300) || !(d > low[j])) {
+      bad = 1;
+      d = 1.0;
     }
-    __syncthreads();
-    if (t == 0) R[j][j] = piv;
+    const double inv = rsqrt_pos(d);
+    if (threadIdx.x == 0) rd[j] = inv;
+    const double rc = c < n ? R[j][c] * inv : 0.0;
+    for (int i = j + 1 + r0; i < n; i += kCholThreads / 64)
+      if (c >= i && c < n) R[i][c] -= (R[j][i] * inv) * rc;
     __syncthreads();
   }
-  // zero strict lower part (it held G)
-  for (int i = 0; i < n; ++i)
-    if (t < i) R[i][t] = 0.0;
+  // rows are still short of their divisions by the pivots
+  for (int i = r0; i < n; i += kCholThreads / 64)
+    if (c > i && c < n) R[i][c] *= rd[i];
   __syncthreads();
-  // X = R^-1, column t by back substitution: R x = e_t
-  if (t < n) {
-    for (int i = n - 1; i >= 0; --i) {
-      double sv = (i == t) ? 1.0 : 0.0;
-      for (int k = i + 1; k < n; ++k) sv -= R[i][k] * X[k][t];
-      X[i][t] = (i > t) ? 0.0 : sv / R[i][i];
-    }
+  for (int i = n - 1; i > 0; --i) {   // row i of R^-1 is final but for its division
+    const double x = c >= i && c < n ? X[c][i] * rd[i] : 0.0;
+    for (int k = r0; k < i; k += kCholThreads / 64)
+      if (c >= i && c < n) X[c][k] -= R[k][i] * x;
+    __syncthreads();
   }
-  __syncthreads();
-  for (int i = 0; i < n; ++i)
-    if (t < n) Rinv[i + t * ldr] = X[i][t];
-  if (t == 0) *status = bad;
+  for (int i = r0; i < n; i += kCholThreads / 64)
+    if (c < n) Rinv[i + c * ldr] = i > c ? 0.0 : X[c][i] * rd[i];
+  if (threadIdx.x == 0) *status = bad;
 }
 
 hipError_t chol_upper_inv(const double* G, int n, int ldg, double* Rinv, int ldr, int* status, hipStream_t s,
                           const double* ref) {
   if (n > 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(chol_upper_inv_kernel, dim3(1), dim3(64), 0, s, G, n, ldg, Rinv, ldr, status, ref);
+  hipLaunchKernelGGL(chol_upper_inv_kernel, dim3(1), dim3(kCholThreads), 0, s, G, n, ldg, Rinv, ldr, status, ref);
   return hipGetLastError();
 }
 
@@ -418,14 +419,15 @@ hipError_t chol_upper_inv(const double* G, int n, int ldg, double* Rinv, int ldr
 // Orthonormal basis of span(S) from its Gram matrix G = S^T S (n x n, n at
 // most the Rayleigh-Ritz order): diagonal-pivoted Cholesky with a rank cut and
 // the inverse of its factor (basis_core.hpp), one workgroup, working copy in
-// LDS up to order kBasisLds.  W (n x rank, leading dimension ldw) = P R^-1;
+// LDS up to order kBasisLds.  Its chain of 2 n steps takes 107 us on average over
+// the restarts of 50 collocation eigenpairs (n about 50 to 130); 206 us with a
+// division per entry of the trailing block, a maximum over the whole workgroup
+// and a sum over the row per entry of the inverse.  W (n x rank, leading dimension ldw) = P R^-1;
 // rank goes to a device int.
 // ---------------------------------------------------------------------------
 constexpr int kBasisThreads = 1024;
 
 struct BasisTeam {
-  double* rv;   // one slot per wave
-  int* ri;
   __device__ int tid() const { return threadIdx.x; }
   __device__ int size() const { return kBasisThreads; }
   __device__ void sync() const { __syncthreads(); }
@@ -433,6 +435,7 @@ struct BasisTeam {
   __device__ static bool better(double v, int i, double bv, int bi) {
     return i >= 0 && (bi < 0 || v > bv || (v == bv && i < bi));
   }
+  // over a wave: every wave looks at all entries, a few per lane, and needs no barrier
   __device__ int argmax(double v, int i) const {
     for (int off = 32; off > 0; off >>= 1) {
       const double ov = __shfl_xor(v, off);
@@ -442,26 +445,15 @@ struct BasisTeam {
         i = oi;
       }
     }
-    if ((threadIdx.x & 63) == 0) {
-      rv[threadIdx.x >> 6] = v;
-      ri[threadIdx.x >> 6] = i;
-    }
-    __syncthreads();
-    double bv = rv[0];
-    int bi = ri[0];
-    for (int w = 1; w < kBasisThreads / 64; ++w)
-      if (better(rv[w], ri[w], bv, bi)) {
-        bv = rv[w];
-        bi = ri[w];
-      }
-    __syncthreads();
-    return bi;
+    return i;
   }
 };
+__device__ inline int argmax_lane(const BasisTeam&) { return threadIdx.x & 63; }
+__device__ inline int argmax_lanes(const BasisTeam&) { return 64; }
 
 // the working copy in LDS up to order kBasisLds, else in `work`
 constexpr int kBasisLds = 136;
-static_assert((kBasisLds * kBasisLds + 2 * kBasisLds) * 8 + (kBasisThreads / 64) * 12 <= 160 * 1024,
+static_assert((kBasisLds * kBasisLds + 2 * kBasisLds) * 8 <= 160 * 1024,
               "the LDS variant of the basis kernel fits in 160 KiB");
 
 template <bool LDS>
@@ -469,10 +461,8 @@ __global__ __launch_bounds__(kBasisThreads) void pchol_basis_kernel(const double
                                                                     double cut, double* __restrict__ work,
                                                                     double* __restrict__ W, int ldw,
                                                                     int* __restrict__ rank) {
-  __shared__ double rv[kBasisThreads / 64];
-  __shared__ int ri[kBasisThreads / 64];
   __shared__ double w_lds[LDS ? kBasisLds * kBasisLds + 2 * kBasisLds : 1];
-  BasisTeam tm{rv, ri};
+  BasisTeam tm;
   const int r = pchol_basis(tm, G, ldg, n, cut, LDS ? w_lds : work, W, ldw);
   if (threadIdx.x == 0) *rank = r;
 }

@@ -3,9 +3,10 @@
 // workgroup (matrix in LDS up to order 128), eigenvalue QR by one wave on a
 // banded copy (LDS up to order 192), then grids for ranking, inverse
 // iteration (one wave per cluster of wanted eigenvalues), back-
-// transformation (one thread per wanted column) and output.
+// transformation (16 lanes per wanted column) and output.
 #include <hip/hip_runtime.h>
 
+#include "back_wave.hpp"
 #include "ka_internal.hpp"
 #include "nonsym_core.hpp"
 
@@ -15,7 +16,6 @@ constexpr int kNsThreads = 512;
 constexpr int kNsHessLds = 128;
 constexpr int kNsBandLds = 192;
 constexpr int kNsMax = 1024;
-constexpr int kNsBackLds = 240;
 constexpr int kNsInvLds = 128;
 
 size_t nonsym_eig_work(int n, int nvec_max) {
@@ -440,30 +440,13 @@ __global__ __launch_bounds__(64) void ns_invit_kernel(double* __restrict__ work,
                 xs);
 }
 
-// one thread per wanted column (real and imaginary parts are separate columns)
-template <bool LDS>
+// the wanted columns (real and imaginary parts are separate columns)
+template <int NS>
 __global__ __launch_bounds__(64) void ns_back_kernel(double* __restrict__ work, int n, int nv, int nvec) {
-  __shared__ double xs[LDS ? kNsBackLds * 64 : 1];
-  __shared__ double vs[kNsMax];
   const NsWork ws = ns_work_split(work, n, nv);
-  const int t = threadIdx.x;
-  const int c = blockIdx.x * 64 + t;
+  const int c = blockIdx.x * 4 + (threadIdx.x >> 4);
   const bool act = c < ns_wanted(ws.wi, n, nvec);
-  double* x = LDS ? xs + t : ws.V + (act ? c : 0);
-  const int stride = LDS ? 64 : nv;
-  if (LDS)
-    for (int i = 0; i < n; ++i) xs[i * 64 + t] = act ? ws.V[(int64_t)i * nv + c] : 0.0;
-  for (int j = n - 3; j >= 0; --j) {
-    const double b = ws.beta[j];
-    if (b == 0.0) continue;                      // uniform over the workgroup
-    const int m = n - j - 1;
-    __syncthreads();
-    for (int i = t; i < m; i += 64) vs[i] = ws.A[(j + 1 + i) + (int64_t)j * n];
-    __syncthreads();
-    if (LDS || act) sym_reflect(vs, m, b, x + (size_t)(j + 1) * stride, stride);
-  }
-  if (LDS && act)
-    for (int i = 0; i < n; ++i) ws.V[(int64_t)i * nv + c] = xs[i * 64 + t];
+  back_wave<NS>(ws.A, ws.beta, n, ws.V, nv, act ? c : 0, act);
 }
 
 // eigenvalues (all n, sorted) and the wanted columns, normalised
@@ -510,16 +493,16 @@ hipError_t nonsym_eig(const double* H, int n, int ldh, int nvec, double* wr, dou
   else
     hipLaunchKernelGGL(ns_qr_ms_kernel<false>, dim3(1), dim3(kNsMsThreads), 0, s, work, n, nv);
   hipLaunchKernelGGL(ns_rank_kernel, dim3((n + 255) / 256), dim3(256), 0, s, work, n, nv);
-  const int g64 = (nv + 63) / 64;
   if (nvec > 0) {
     if (n <= kNsInvLds)
       hipLaunchKernelGGL(ns_invit_kernel<true>, dim3(nv), dim3(64), 0, s, work, n, nv, nvec);
     else
       hipLaunchKernelGGL(ns_invit_kernel<false>, dim3(nv), dim3(64), 0, s, work, n, nv, nvec);
-    if (n <= kNsBackLds)
-      hipLaunchKernelGGL(ns_back_kernel<true>, dim3(g64), dim3(64), 0, s, work, n, nv, nvec);
-    else
-      hipLaunchKernelGGL(ns_back_kernel<false>, dim3(g64), dim3(64), 0, s, work, n, nv, nvec);
+    const auto back = n <= 128   ? ns_back_kernel<8>
+                      : n <= 256 ? ns_back_kernel<16>
+                      : n <= 512 ? ns_back_kernel<32>
+                                 : ns_back_kernel<64>;
+    hipLaunchKernelGGL(back, dim3((nv + 3) / 4), dim3(64), 0, s, work, n, nv, nvec);
   }
   hipLaunchKernelGGL(ns_out_kernel, dim3((n + 255) / 256), dim3(256), 0, s, work, n, nv, nvec, wr, wi, S, lds,
                      status);

@@ -1,12 +1,13 @@
 // Device driver of the small symmetric eigensolve (sym_core.hpp) used by the
 // Galerkin Rayleigh-Ritz step: the tridiagonalisation runs as one workgroup
 // (working matrix in LDS up to order 128), the other stages as grids with one
-// wave per eigenvalue, one thread per cluster and one thread per vector; only
-// the leading nvec eigenvectors are formed.
+// wave per eigenvalue, one thread per cluster and 16 lanes per vector; only the
+// leading nvec eigenvectors are formed.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
+#include "back_wave.hpp"
 #include "ka_internal.hpp"
 #include "sym_core.hpp"
 
@@ -16,7 +17,6 @@ constexpr int kTriThreads = 512;
 constexpr int kTriLds = 128;
 constexpr int kSymTriMax = 1024;
 constexpr int kTriNb = kSymNbMax;   // panel width of the blocked reduction
-constexpr int kBackLds = 240;
 
 size_t sym_tri_work(int n) { return sym_tri_work_doubles(n); }
 
@@ -130,77 +130,11 @@ __global__ __launch_bounds__(NT) void sym_invit_kernel(double* __restrict__ work
   }
 }
 
-// one thread per wanted vector; the workgroup's 64 vectors are staged in LDS
-// (element i of vector t at xs[i * 64 + t]) up to order kBackLds
-
-template <bool LDS>
-__global__ __launch_bounds__(64) void sym_back_kernel(double* __restrict__ work, int n, int nvec) {
-  __shared__ double xs[LDS ? kBackLds * 64 : 1];
-  __shared__ double vs[kSymTriMax];
-  const SymWork sw = sym_work_split(work, n);
-  const int t = threadIdx.x;
-  const int k = n - nvec + blockIdx.x * 64 + t;
-  const bool act = k < n;
-  double* x = LDS ? xs + t : sw.V + (act ? k : 0);
-  const int stride = LDS ? 64 : n;
-  if (LDS)
-    for (int i = 0; i < n; ++i) xs[i * 64 + t] = act ? sw.V[(int64_t)i * n + k] : 0.0;
-  for (int j = n - 3; j >= 0; --j) {
-    const double b = sw.beta[j];
-    if (b == 0.0) continue;                      // uniform over the workgroup
-    const int m = n - j - 1;
-    __syncthreads();
-    for (int i = t; i < m; i += 64) vs[i] = sw.A[(j + 1 + i) + (int64_t)j * n];
-    __syncthreads();
-    if (LDS || act) sym_reflect(vs, m, b, x + (size_t)(j + 1) * stride, stride);
-  }
-  if (LDS && act)
-    for (int i = 0; i < n; ++i) sw.V[(int64_t)i * n + k] = xs[i * 64 + t];
-}
-
-// Above order kBackLds: one wave per 4 vectors, 16 lanes per vector.  Lane r
-// of a vector holds its elements r, r + 16, ... (NS of them) in registers;
-// for each reflector the 16 lanes form the dot product with a fixed
-// butterfly, then update their own elements.  No barriers: every wave walks
-// the reflectors (read through the cache) on its own.
 template <int NS>
-__global__ __launch_bounds__(64) void sym_back_wave_kernel(double* __restrict__ work, int n, int nvec) {
+__global__ __launch_bounds__(64) void sym_back_kernel(double* __restrict__ work, int n, int nvec) {
   const SymWork sw = sym_work_split(work, n);
-  const int lane = threadIdx.x & 63, r = lane & 15;
-  const int k = n - nvec + blockIdx.x * 4 + (lane >> 4);
-  const bool act = k < n;
-  const int kk = act ? k : n - 1;
-  double x[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const int i = r + 16 * s;
-    x[s] = (i < n) ? sw.V[(int64_t)i * n + kk] : 0.0;
-  }
-  for (int j = n - 3; j >= 0; --j) {
-    const double b = sw.beta[j];
-    if (b == 0.0) continue;                      // uniform over the grid
-    const double* v = sw.A + (int64_t)j * n;     // reflector: rows j + 1 .. n - 1 of column j
-    double dot = 0.0;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int i = r + 16 * s;
-      if (i > j && i < n) dot += v[i] * x[s];
-    }
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 16);
-    const double sc = b * dot;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {          // v again, now from the cache
-      const int i = r + 16 * s;
-      if (i > j && i < n) x[s] -= sc * v[i];
-    }
-  }
-  if (act)
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int i = r + 16 * s;
-      if (i < n) sw.V[(int64_t)i * n + k] = x[s];
-    }
+  const int k = n - nvec + blockIdx.x * 4 + (threadIdx.x >> 4);
+  back_wave<NS>(sw.A, sw.beta, n, sw.V, n, k < n ? k : n - 1, k < n);
 }
 
 // theta descending (all n); S column k (k < nvec) = vector n-1-k
@@ -234,12 +168,11 @@ hipError_t sym_eig_tri(const double* H, int n, int ldh, int nvec, double* theta,
     else
       hipLaunchKernelGGL((sym_invit_kernel<false, 64, 1>), dim3(g64), dim3(64), 0, s, work, n, nvec);
     const int g4 = (nvec + 3) / 4;
-    if (n <= kBackLds)
-      hipLaunchKernelGGL(sym_back_kernel<true>, dim3(g64), dim3(64), 0, s, work, n, nvec);
-    else if (n <= 512)
-      hipLaunchKernelGGL(sym_back_wave_kernel<32>, dim3(g4), dim3(64), 0, s, work, n, nvec);
-    else
-      hipLaunchKernelGGL(sym_back_wave_kernel<64>, dim3(g4), dim3(64), 0, s, work, n, nvec);
+    const auto back = n <= 128   ? sym_back_kernel<8>
+                      : n <= 256 ? sym_back_kernel<16>
+                      : n <= 512 ? sym_back_kernel<32>
+                                 : sym_back_kernel<64>;
+    hipLaunchKernelGGL(back, dim3(g4), dim3(64), 0, s, work, n, nvec);
   }
   const int64_t nq = std::max<int64_t>((int64_t)n * nvec, n);
   hipLaunchKernelGGL(sym_out_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, s, work, n, nvec, theta, S,
