@@ -23,6 +23,16 @@ __device__ __forceinline__ double row_sum16(double x) {
   return x;
 }
 
+// the sum over a wave, the same in each lane
+__device__ __forceinline__ double wave_sum(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, row_sum16(x));
+  auto row = [&](int l) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, l), hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  };
+  return (row(0) + row(16)) + (row(32) + row(48));
+}
+
 // One wave per 4 vectors, 16 lanes per vector.  Lane r of a vector holds its
 // elements r, r + 16, ... (NS of them, n <= 16 NS) in registers; for each
 // reflector the 16 lanes form the dot product, then update their own elements.

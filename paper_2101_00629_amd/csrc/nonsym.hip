@@ -32,7 +32,7 @@ struct NsTeam {
   __device__ int size() const { return NT; }
   __device__ void sync() const { __syncthreads(); }
   __device__ double sum(double x) const {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+    x = wave_sum(x);
     if (NT == 64) return x;
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
     __syncthreads();
@@ -66,6 +66,16 @@ struct NsTeam {
   }
 };
 
+// Hessenberg reduction with the matrix in LDS: four threads per dot product (223
+// us on average in the solve for 50 collocation pairs; 339 us with one, sums by
+// shuffles and the matrix read a column at a time)
+struct NsLdsTeam : NsTeam<kNsThreads> {
+  double* part;
+};
+__device__ inline int dot_groups(const NsLdsTeam&) { return kNsThreads / kNsHessLds; }
+__device__ inline int dot_len(const NsLdsTeam&) { return kNsHessLds; }
+__device__ inline double* dot_part(const NsLdsTeam& tm) { return tm.part; }
+
 template <bool LDS>
 __global__ __launch_bounds__(kNsThreads) void ns_hess_kernel(const double* __restrict__ H, int n, int ldh,
                                                              double* __restrict__ work, int nv) {
@@ -75,11 +85,20 @@ __global__ __launch_bounds__(kNsThreads) void ns_hess_kernel(const double* __res
   const NsWork ws = ns_work_split(work, n, nv);
   const int ld = LDS ? n + 1 : n;
   double* A = LDS ? A_lds : ws.A;
-  for (int j = 0; j < n; ++j)
-    for (int i = threadIdx.x; i < n; i += kNsThreads) A[i + (size_t)j * ld] = H[i + (int64_t)j * ldh];
+  // (several columns at once: a column at a time waits for memory n times)
+  for (int i = threadIdx.x % kNsHessLds; i < n; i += kNsHessLds)
+#pragma unroll 8
+    for (int j = threadIdx.x / kNsHessLds; j < n; j += kNsThreads / kNsHessLds)
+      A[i + (size_t)j * ld] = H[i + (int64_t)j * ldh];
   __syncthreads();
-  NsTeam<kNsThreads> tm{red};
-  ns_hessenberg<LDS ? 2 : 8>(tm, A, ld, n, ws.hsub, ws.beta, v, w);
+  __shared__ double part[LDS ? kNsThreads : 1];
+  if constexpr (LDS) {
+    NsLdsTeam tm{{red}, part};
+    ns_hessenberg<2>(tm, A, ld, n, ws.hsub, ws.beta, v, w);
+  } else {
+    NsTeam<kNsThreads> tm{red};
+    ns_hessenberg<8>(tm, A, ld, n, ws.hsub, ws.beta, v, w);
+  }
   if (LDS)
     for (int j = 0; j < n; ++j)
       for (int i = threadIdx.x; i < n; i += kNsThreads) ws.A[i + (size_t)j * n] = A[i + (size_t)j * ld];
@@ -465,15 +484,14 @@ __global__ __launch_bounds__(256) void ns_out_kernel(const double* __restrict__ 
   const int c0 = first ? c : c - 1;
   const bool pair = ws.wi[c0] > 0.0;
   double s = 0.0;
+#pragma unroll 8
   for (int i = 0; i < n; ++i) {
-    const double a = ws.V[(int64_t)i * nv + c0];
+    const double a = ws.V[(int64_t)i * nv + c0], b = pair ? ws.V[(int64_t)i * nv + c0 + 1] : 0.0;
     s += a * a;
-    if (pair) {
-      const double b = ws.V[(int64_t)i * nv + c0 + 1];
-      s += b * b;
-    }
+    s += b * b;
   }
   const double sc = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+#pragma unroll 8
   for (int i = 0; i < n; ++i) S[i + (int64_t)c * lds] = ws.V[(int64_t)i * nv + c] * sc;
 }
 

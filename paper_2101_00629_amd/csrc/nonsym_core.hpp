@@ -161,6 +161,9 @@ KA_HD void ns_hessenberg(Team& tm, double* A, int ld, int n, double* hsub, doubl
       // enough are in flight when A lives in device memory; the dot products
       // keep eight partial sums added in a fixed tree.
       // left: A[j+1:, c] -= b v (v^T A[j+1:, c]) for c > j (a thread per column)
+      if (dot_groups(tm) > 1 && n <= dot_len(tm))
+        team_dots(tm, &AH(j + 1, j + 1), ld, 1, m, m, v, b, w + j + 1);
+      else
       for (int c = j + 1 + t; c < n; c += NT) {
         const double* col = &AH(j + 1, c);
         double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -198,6 +201,9 @@ KA_HD void ns_hessenberg(Team& tm, double* A, int ld, int n, double* hsub, doubl
       }
       tm.sync();
       // right: A[r, j+1:] -= b (A[r, j+1:] v) v^T for every row (a thread per row)
+      if (dot_groups(tm) > 1 && n <= dot_len(tm))
+        team_dots(tm, &AH(0, j + 1), 1, ld, n, m, v, b, w);
+      else
       for (int r = t; r < n; r += NT) {
         const double* row = &AH(r, j + 1);
         double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -1000,10 +1006,19 @@ KA_HD void ns_invit_team(Team& tm, const double* HT, const double* hsub, int n, 
     // ---- LU of B = Hh - lambda I --------------------------------------------------------
     // The planes start as the upper triangle of B (row r, columns >= r), so
     // step j reads row j+1 of B from fast memory before overwriting it.
-    for (int r = 0; r < n; ++r)
-      for (int cc = r + t; cc < n; cc += NT) {
-        UR(r, cc) = HT[(size_t)r * n + cc] - (cc == r ? lr : 0.0);
-        if (cplx) UI(r, cc) = (cc == r ? -li : 0.0);
+    // (a column per thread, eight rows' loads at a time)
+    for (int cc = t; cc < n; cc += NT)
+      for (int r0 = 0; r0 <= cc; r0 += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = HT[(size_t)(r0 + u <= cc ? r0 + u : cc) * n + cc];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int r = r0 + u;
+          if (r > cc) continue;
+          UR(r, cc) = x[u] - (cc == r ? lr : 0.0);
+          if (cplx) UI(r, cc) = (cc == r ? -li : 0.0);
+        }
       }
     tm.sync();
     double sub_next = n > 1 ? hsub[0] : 0.0;

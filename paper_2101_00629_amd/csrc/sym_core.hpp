@@ -75,6 +75,46 @@ KA_HD inline double sym_copysign(double a, double b) { return b >= 0.0 ? fabs(a)
 // (enough in flight to cover the latency of a matrix held in device memory)
 constexpr int kSymBatch = 8;
 
+// A team may share each dot product of a matrix with a vector among several of
+// its threads (dot_groups(tm) of them, for up to dot_len(tm) products at a time)
+// through dot_part(tm), groups x len doubles of team-shared scratch; by default
+// a thread forms a whole one.
+template <class Team>
+KA_HD int dot_groups(const Team&) { return 1; }
+template <class Team>
+KA_HD int dot_len(const Team&) { return 0; }
+template <class Team>
+KA_HD double* dot_part(const Team&) { return nullptr; }
+
+// w[r] = b sum_i a[r rs + i is] v[i], r < len, i < m, by a team with dot_groups
+// (tm.size() = groups x dot_len); ends without a barrier.
+template <class Team>
+KA_HD KA_FORCEINLINE void team_dots(Team& tm, const double* a, size_t rs, size_t is, int len, int m, const double* v,
+                                    double b, double* w) {
+  const int t = tm.tid(), L = dot_len(tm), DG = dot_groups(tm), r = t % L, g = t / L;
+  double* part = dot_part(tm);
+  if (r < len) {
+    const double* x = a + r * rs;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    int i = g;
+    for (; i + 3 * DG < m; i += 4 * DG) {
+      double y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) y[u] = x[(size_t)(i + u * DG) * is];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s[u] += y[u] * v[i + u * DG];
+    }
+    for (; i < m; i += DG) s[0] += x[(size_t)i * is] * v[i];
+    part[g * L + r] = (s[0] + s[1]) + (s[2] + s[3]);
+  }
+  tm.sync();
+  if (t < len) {
+    double s = part[t];
+    for (int k = 1; k < DG; ++k) s += part[k * L + t];
+    w[t] = b * s;
+  }
+}
+
 template <class Team>
 KA_HD void sym_tridiagonalize(Team& tm, double* A, int n, double* d, double* e, double* beta, double* v,
                               double* w) {
@@ -102,6 +142,9 @@ KA_HD void sym_tridiagonalize(Team& tm, double* A, int n, double* d, double* e, 
       double* A22 = A + (j + 1) + (size_t)(j + 1) * n;
       // w = b A22 v: a thread per row, kSymBatch columns at a time with their
       // loads issued together (eight partial sums, added in a fixed tree)
+      if (dot_groups(tm) > 1 && m <= dot_len(tm))
+        team_dots(tm, A22, 1, n, m, m, v, b, w);
+      else
       for (int r = t; r < m; r += NT) {
         const double* row = A22 + r;
         double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
