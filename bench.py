@@ -527,7 +527,8 @@ def roofline(res, name, precision):
     half to two thirds of the cycles at b = 64.  The FP32 record also gives the
     rate against the FP32 units it no longer runs on (mfma_frac, serial_frac)."""
     a = res["achieved"]
-    rec = {"kernel": "gamma_f16x3_kernel" if precision == "fp32" else "gamma_bf16x3_kernel",
+    rec = {"kernel": "gamma_f16x3_kernel" if precision == "fp32" else
+           "gamma_f16x3_kernel (Gaussian), gamma_bf16x3_kernel (exponential)",
            "launches": res["launches"], "kernel_ms": res["gl_ms"],
            "kernel_share_of_step": res["gl_ms"] / 1e3 / res["elapsed"],
            "pairs_per_s": a, "valu_peak_pairs_per_s": res["valu_peak"], "valu_frac": a / res["valu_peak"]}

@@ -40,8 +40,8 @@ __device__ __forceinline__ double wave_sum(double x) {
 // ahead.  Reflector j: rows j + 1 .. n - 1 of column j of A (n x n), times beta[j].
 // Element i of vector `col` at V[i ld + col].
 //
-// The time is the chain over the reflectors, 0.5 us each: 59 us for the 66
-// vectors of order 116 of a Rayleigh-Ritz step.  (303 us with one thread per
+// The time is the chain over the reflectors, about 0.5 us each: 59 us for a
+// Rayleigh-Ritz step of the solve for 50 Galerkin pairs with blocks of 16.  (303 us with one thread per
 // vector and a reflector at a time through LDS; 150 us like this without
 // leaving out the elements a reflector does not reach.)
 template <int NS>
