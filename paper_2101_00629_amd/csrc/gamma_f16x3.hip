@@ -86,6 +86,11 @@ __device__ __forceinline__ uint32_t pack_h2(float a, float b) {
 
 __device__ __forceinline__ float half_of(float x) { return (float)(_Float16)x; }
 
+// a value that is the same in every lane, in a scalar register
+__device__ __forceinline__ float uniform(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+
 // Scaled FP64 coordinate relative to the launch's centre
 __device__ __forceinline__ double lattice_coord(const GammaLaunch& a, float x, double c) {
   return (double)x * ((double)a.coord_scale + (double)a.coord_scale_lo) - c;
@@ -372,8 +377,18 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
   // just short of taking Gamma at the distance of the row from the group's box
   // to 2^15; the inverse goes to s_inv for the sums of the group (`par` its
   // parity).  Row points are read from LDS: this runs once per group.
+  // The distance must not come out larger than the kernel's exponents have it,
+  // or Gamma passes 2^16.  Box and row are rounded to FP32 relative to the
+  // launch's centre, the exponents' coordinates relative to the workgroup's.  On
+  // the lattice (below 31 units) that is nothing next to the factor of two in
+  // hand; differences may be of any size, and there each gap is shortened by the
+  // roundings it can hold: one of row and box, two each of the coordinates in a
+  // difference, 6 of 2^-24, taken as 8.
   float Sg[RB];
   float gb[6];   // box of the next group
+  const float off[3] = {uniform(__builtin_fabsf((float)cl[0]) + __builtin_fabsf(c0)),
+                        uniform(__builtin_fabsf((float)cl[1]) + __builtin_fabsf(c1)),
+                        uniform(__builtin_fabsf((float)cl[2]) + __builtin_fabsf(c2))};
   auto load_box = [&](int64_t g) {
     const uniform_float* b = (const uniform_float*)(uintptr_t)(a.gbox + 8 * (g < a.ngroups ? g : 0));
 #pragma unroll
@@ -389,7 +404,13 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
       float d = 0.f;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        const float x = s_row[k][r], gap = fmaxf(fmaxf(gb[k] - x, x - gb[3 + k]), 0.f);
+        const float x = s_row[k][r];
+        float gap = fmaxf(gb[k] - x, x - gb[3 + k]);
+        if constexpr (!GRAM) {
+          const float far = fmaxf(__builtin_fabsf(x), fmaxf(__builtin_fabsf(gb[k]), __builtin_fabsf(gb[3 + k])));
+          gap -= 0x1p-21f * (far + off[k]);
+        }
+        gap = fmaxf(gap, 0.f);
         d += KERNEL == KA_GAUSSIAN ? gap * gap : gap;
       }
       const int up = 15 + (int)fminf(0.999f * d, 110.f);
@@ -684,9 +705,9 @@ void gamma_f16x3_kernel(GammaLaunch a) {
   launch_centre(a, cl);
   float c0, c1, c2;
   (void)gram_rows<RB>(a, rblk, s_box, c0, c1, c2);
-  c0 = finite_bits(c0) ? c0 : 0.f;   // (rows at infinity)
-  c1 = finite_bits(c1) ? c1 : 0.f;
-  c2 = finite_bits(c2) ? c2 : 0.f;
+  c0 = uniform(finite_bits(c0) ? c0 : 0.f);   // (rows at infinity)
+  c1 = uniform(finite_bits(c1) ? c1 : 0.f);
+  c2 = uniform(finite_bits(c2) ? c2 : 0.f);
   // the rows' points relative to the launch's centre, whether they are on the
   // lattice, and the flags of the columns' groups
   int flags = 0;
