@@ -315,9 +315,25 @@ constexpr int kYRing = 3;     // tiles of Y in LDS
 constexpr int kVm0 = (7 << 4) | (15 << 8);   // s_waitcnt: vmcnt(0) alone
 constexpr int kXRing = 4;     // tiles of column operands in LDS
 
-// Scaled FP32 coordinate relative to a workgroup's centre (difference form)
+// Scaled FP32 coordinate relative to a workgroup's centre (difference form; row_centre)
 __device__ __forceinline__ float centred(const GammaLaunch& a, float x, float c) {
   return __builtin_fmaf(x, a.coord_scale_lo, __builtin_fmaf(x, a.coord_scale, -c));
+}
+
+// Centre of a workgroup's rows along direction k for the difference form: the
+// middle of their box, or zero where that would cost a row accuracy.  A
+// coordinate is rounded at its distance from the centre, half the box's extent
+// at most.  That is taken if no row lies nearer to zero than that, or if it is
+// below 16 (Gaussian) or 32 scaled units: two coordinates 2^-21 (2^-20) off
+// change an exponent d^2 with d <= 2 by 4e-6 at most (a distance by 2e-6).  One
+// row far from the others of its block must not round theirs away.
+template <int KERNEL>
+__device__ __forceinline__ float row_centre(const float (*s_box)[8], int k, float mid) {
+  const float lo = fminf(fminf(s_box[0][k], s_box[1][k]), fminf(s_box[2][k], s_box[3][k]));
+  const float hi = fmaxf(fmaxf(s_box[0][4 + k], s_box[1][4 + k]), fmaxf(s_box[2][4 + k], s_box[3][4 + k]));
+  const float half = 0.5f * (hi - lo), nearest = fmaxf(lo, -hi);
+  // (rows at infinity: zero)
+  return finite_bits(mid) && half <= fmaxf(nearest, KERNEL == KA_GAUSSIAN ? 16.f : 32.f) ? mid : 0.f;
 }
 
 template <int KERNEL, int B, int RB, bool GRAM>
@@ -705,9 +721,9 @@ void gamma_f16x3_kernel(GammaLaunch a) {
   launch_centre(a, cl);
   float c0, c1, c2;
   (void)gram_rows<RB>(a, rblk, s_box, c0, c1, c2);
-  c0 = uniform(finite_bits(c0) ? c0 : 0.f);   // (rows at infinity)
-  c1 = uniform(finite_bits(c1) ? c1 : 0.f);
-  c2 = uniform(finite_bits(c2) ? c2 : 0.f);
+  c0 = uniform(row_centre<KERNEL>(s_box, 0, c0));
+  c1 = uniform(row_centre<KERNEL>(s_box, 1, c1));
+  c2 = uniform(row_centre<KERNEL>(s_box, 2, c2));
   // the rows' points relative to the launch's centre, whether they are on the
   // lattice, and the flags of the columns' groups
   int flags = 0;

@@ -70,3 +70,19 @@ def test_strip_far_from_the_middle_row(kernel, b):
         others = np.arange(n) // rows != (n // 2) // rows
         err = _errors(kernel, 1.0, X[others], X, Y, Z[others])
         assert err.max() < 1.1e-4, (far, err.max())
+
+
+@pytest.mark.parametrize("kernel", [K.KA_GAUSSIAN, K.KA_EXP_L1])
+@pytest.mark.parametrize("b", [16, 64])
+def test_far_row_leaves_its_block(kernel, b):
+    # one row of a block far off, in turn the launch's middle row and another
+    nr, ell = 1500 if b == 64 else 3000, 0.5
+    C, Y = tensor_grid_points((23, 23, 23)), normal_block(23, 23 ** 3, b, dtype=np.float32)
+    for row in (3, nr // 2):
+        for f in (1e2, 1e3, 1e5, 1e7, 1e30):
+            X = uniform_points(21, nr)
+            X[row] = f
+            Z = _product(kernel, ell, X, C, Y)
+            assert (Z[row] == 0).all()
+            err = _errors(kernel, ell, X, C, Y, Z)
+            assert err.max() < 1e-5, (row, f, err.max())
