@@ -473,7 +473,7 @@ static ModeArgs mode_args(const Block& in, const Block& out, int dims[3], int mo
   return a;
 }
 
-int gamma_step(Problem* P, const float* Y, float* Z, hipStream_t s) {
+int gamma_step(Problem* P, const float* Y, float* Z, int nv, hipStream_t s) {
   GammaLaunch g;
   g.xr = P->rows;
   g.xr_stride = 4;
@@ -491,6 +491,7 @@ int gamma_step(Problem* P, const float* Y, float* Z, hipStream_t s) {
   g.coord_scale = P->coord_scale;
   g.coord_scale_lo = 0.0f;   // prescaled in FP64
   g.out_scale = P->out_scale;
+  g.nv = nv;
   g.nsplit = 1;
   g.cols_per_split = 0;
   g.row_blocks = 0;
@@ -597,6 +598,7 @@ GammaLaunch gamma_job(Problem* P) {
   g.coord_scale = P->coord_scale;
   g.coord_scale_lo = 0.0f;   // prescaled in FP64
   g.out_scale = P->out_scale;
+  g.nv = P->b;
   const GammaPlan gp = gamma_plan(g.nr, g.nc, P->b, P->d.precision);
   g.nsplit = gp.nsplit;
   g.cols_per_split = gp.cols_per_split;
@@ -609,7 +611,7 @@ GammaLaunch gamma_job(Problem* P) {
 int apply_block(Problem* P, int form, const double* X, int64_t ldx, double* Y, int64_t ldy, int nv, hipStream_t s) {
   int rc;
   if ((rc = apply_pre(P, form, X, ldx, nv, s))) return rc;
-  if ((rc = gamma_step(P, P->w32b, P->w32a, s))) return rc;
+  if ((rc = gamma_step(P, P->w32b, P->w32a, nv, s))) return rc;
   return apply_post(P, form, Y, ldy, nv, s);
 }
 

@@ -115,6 +115,7 @@ int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, in
   g.ys = nullptr;   // launch_gamma places it in the workspace
   g.coord_scale = kernel_coord_scale(kernel, ell, &g.coord_scale_lo);
   g.out_scale = (float)(sigma * sigma);
+  g.nv = b;
   g.nsplit = 1;
   g.cols_per_split = 0;
   g.row_blocks = 0;

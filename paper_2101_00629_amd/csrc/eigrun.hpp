@@ -31,6 +31,7 @@ class EigRun {
   EigRun& operator=(const EigRun&) = delete;
   int start();                       // workspace, start block
   int pre_apply();                   // operator steps up to the kernel product of the pending block
+  int block_width() const { return pw_; }   // vectors of the pending block
   int post_apply(bool& done);        // the rest of the step; done = stop iterating
   int finish(double* lambda_host, double* V_dev, ka_info* info);
   size_t bytes() const { return cap_; }

@@ -548,7 +548,7 @@ int eigs(Problem* P, int M, double tol, int maxit, double* lambda_host, double* 
   bool done = false;
   while (!done) {
     KA_TRY(run.pre_apply());
-    KA_TRY(gamma_step(P, P->w32b, P->w32a, P->stream));
+    KA_TRY(gamma_step(P, P->w32b, P->w32a, run.block_width(), P->stream));
     KA_TRY(run.post_apply(done));
   }
   return run.finish(lambda_host, V_dev, info);

@@ -139,7 +139,9 @@ __device__ __forceinline__ LatticePoint lattice_point(const GammaLaunch& a, cons
 // Y's fragments lie as the product's LDS tiles hold them: entry (ks NT + t) 64
 // + lane of a 64-column tile is the MFMA B operand of vectors 16 t .. + 15 and
 // columns 32 ks .. + 31 (lane 16 g + n: vector n, columns 8 g .. + 7), hi parts
-// first.  Gram operands: fragment (ks, w), lane 16 q + m is block q of column
+// first.  Vectors that do not count (a block application of fewer than b leaves
+// there what an earlier one wrote) are taken as zero: the groups' flags are
+// common to all vectors.  Gram operands: fragment (ks, w), lane 16 q + m is block q of column
 // 32 ks + 8 (m / 4) + 4 w + m % 4, the column whose exponent the product wants
 // in result m % 4 of lane group m / 4.
 // ---------------------------------------------------------------------------
@@ -155,7 +157,7 @@ __device__ __forceinline__ void split16_group(const GammaLaunch& a, int kernel, 
   const int64_t c0 = g * G + part * CPT;
   float y[CPT];
 #pragma unroll
-  for (int u = 0; u < CPT; ++u) y[u] = c0 + u < a.nc ? a.Y[(c0 + u) * B + j] : 0.f;
+  for (int u = 0; u < CPT; ++u) y[u] = c0 + u < a.nc && j < a.nv ? a.Y[(c0 + u) * B + j] : 0.f;
   float m = 0.f;
   int flag = 0;
 #pragma unroll

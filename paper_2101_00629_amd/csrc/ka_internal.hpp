@@ -31,6 +31,7 @@ struct GammaLaunch {
   float coord_scale;      // applied to every coordinate on load
   float coord_scale_lo;   // what coord_scale leaves of the FP64 scale (split FP16)
   float out_scale;        // sigma^2
+  int nv;                 // vectors that count: the others of the b may hold anything, and their results are not used
   int nsplit;             // filled by launch_gamma
   int64_t cols_per_split; // filled by launch_gamma
   int64_t row_blocks;     // filled by launch_gamma
@@ -248,7 +249,8 @@ int solve_block(Problem* P, int op, double* X, int64_t ld, int nv, hipStream_t s
 int apply_pre(Problem* P, int form, const double* X, int64_t ldx, int nv, hipStream_t s);
 int apply_post(Problem* P, int form, double* Y, int64_t ldy, int nv, hipStream_t s);
 GammaLaunch gamma_job(Problem* P);
-int gamma_step(Problem* P, const float* Y, float* Z, hipStream_t s);
+// kernel product of the block that apply_pre(nv vectors) left in Y
+int gamma_step(Problem* P, const float* Y, float* Z, int nv, hipStream_t s);
 // Device memory for a problem: from its region when it has one, else
 // hipMalloc (recorded in allocs).  nullptr when it does not fit or fails.
 void* problem_alloc(Problem* P, size_t bytes);

@@ -264,8 +264,8 @@ void finish_request(Server* S, const Request& r, int status, double t_admit, Eig
   S->done.push_back(res);
 }
 
-// One block application's kernel product for the solve on `P`.
-int product(Server* S, Problem* P, hipEvent_t ready) {
+// One block application's kernel product (nv vectors) for the solve on `P`.
+int product(Server* S, Problem* P, int nv, hipEvent_t ready) {
   GammaLaunch a = gamma_job(P);
   const int64_t items = work_items(a, P->b);
   if (items >= kDirectItems) {
@@ -274,7 +274,7 @@ int product(Server* S, Problem* P, hipEvent_t ready) {
       std::lock_guard<std::mutex> g(S->mu);
       S->direct_launches++;
     }
-    return gamma_step(P, P->w32b, P->w32a, P->stream);
+    return gamma_step(P, P->w32b, P->w32a, nv, P->stream);
   }
   PendingGamma pg;
   pg.job.a = a;
@@ -383,7 +383,7 @@ void worker_main(Server* S) {
     bool done = false;
     while (rc == KA_OK && !done) {
       rc = run->pre_apply();
-      if (rc == KA_OK) rc = product(S, P, ready);
+      if (rc == KA_OK) rc = product(S, P, run->block_width(), ready);
       if (rc == KA_OK) rc = run->post_apply(done);
     }
     if (solving_flag) {
