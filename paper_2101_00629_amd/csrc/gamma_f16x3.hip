@@ -18,9 +18,15 @@
 // scale per group of 512 columns that takes its largest entry there just below
 // 2^15, and every row a scale per group that takes Gamma at the row's distance
 // from the group's bounding box just below 2^15 (both powers of two; the FP64
-// totals undo them).  What is lost is relative accuracy below 2^-16 of the
-// largest Gamma or Y of a group, an absolute 2^-40 of that.  Groups with
-// values that are not finite are added pair by pair (no scale would hold).
+// totals undo them).  Below 2^-16 of its largest a value loses bits, below 2^-40
+// all of them.  What would show that in a result is formed in FP32:
+// - columns with an entry that is not finite or below 2^-22 of its vector's
+//   largest in the group (2^-18 off in FP16 parts), and all columns of a group
+//   with no more than 64 that are not zero, are marked by the pre-pass, left out
+//   of the FP16 operands and added as they stand; where half of an item's
+//   columns are marked, all of it is formed so;
+// - rows whose results are too small for what the groups' boxes promise, which
+//   may be what was lost (lossy_results), are done again.
 //
 // Exponents (Gaussian).  16 x 16 exponents -|x - y|^2 come from one
 // v_mfma_f32_16x16x32_f16.  Coordinates (scaled, relative to the launch's
@@ -70,7 +76,10 @@ constexpr int kPreThreads = 1024;           // of the pre-pass, one workgroup pe
 constexpr int kXEntries = 256;              // uint4 of column operands per tile
 constexpr float kLat = 64.f;                // 1 / spacing of the coordinate lattice
 
-enum { kBadValue = 1, kOffLattice = 2 };   // flags of a column group
+constexpr int kFewColumns = 64;             // a group with no more columns that are not zero has them added in FP32
+constexpr int kNoScale = 200;               // "scale" of a vector that is zero in a group
+
+enum { kOffLattice = 1, kGaps = 2, kMarks = 4 };   // flags of a column group, and kMarks times its columns in FP32
 
 template <int B>
 constexpr int h16_entries() { return (kCT / 32) * (B / 16) * 64; }   // uint4 per 64-column tile and part
@@ -145,43 +154,63 @@ __device__ __forceinline__ LatticePoint lattice_point(const GammaLaunch& a, cons
 // 32 ks + 8 (m / 4) + 4 w + m % 4, the column whose exponent the product wants
 // in result m % 4 of lane group m / 4.
 // ---------------------------------------------------------------------------
+struct SplitShared {
+  float b[kPreThreads / 64][8];           // boxes of the waves' columns
+  uint32_t bad[kGroup / 32], nz[kGroup / 32], point[kGroup / 32];   // a bit per column
+  uint32_t gap[2];                        // a bit per vector
+  int flag;
+};
+
 template <int B>
 __device__ __forceinline__ void split16_group(const GammaLaunch& a, int kernel, int64_t g, float (*s_m)[B], float* s_up,
-                                              int* s_flag, float (*s_b)[8]) {
+                                              SplitShared& sh) {
   constexpr int NT = B / 16;
   constexpr int G = kGroup, GT = kGroupTiles;
   constexpr int PARTS = kPreThreads / B;
-  constexpr int CPT = G / PARTS;        // columns per thread: 8, 16 or 32
+  constexpr int CPT = G / PARTS;        // columns per thread: 8, 16 or 32; a wave has 32
   constexpr int E = h16_entries<B>();
   const int j = threadIdx.x % B, part = threadIdx.x / B;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int bit0 = part * CPT % 32;     // this thread's first column in its wave's word
   const int64_t c0 = g * G + part * CPT;
   float y[CPT];
 #pragma unroll
   for (int u = 0; u < CPT; ++u) y[u] = c0 + u < a.nc && j < a.nv ? a.Y[(c0 + u) * B + j] : 0.f;
-  float m = 0.f;
-  int flag = 0;
+  uint32_t most = 0, least = ~0u;   // of the entries' magnitudes, as bits
 #pragma unroll
   for (int u = 0; u < CPT; ++u) {
-    if (!finite_bits(y[u])) flag |= kBadValue;
-    m = fmaxf(m, __builtin_fabsf(y[u]));
+    const uint32_t v = __builtin_bit_cast(uint32_t, y[u]) & 0x7fffffffu;
+    most = most > v ? most : v;
+    least = least < v ? least : v;
   }
-  if (threadIdx.x == 0) *s_flag = 0;
+  float m = __builtin_bit_cast(float, most);   // largest finite entry
+  if (!finite_bits(m)) {
+    m = 0.f;
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) m = fmaxf(m, finite_bits(y[u]) ? __builtin_fabsf(y[u]) : 0.f);
+  }
+  if (threadIdx.x == 0) sh.flag = 0;
+  if (threadIdx.x < 2) sh.gap[threadIdx.x] = 0;
   s_m[part][j] = m;
   // the column points: their places on the lattice, and the group's box
   double c[3];
   launch_centre(a, c);
   LatticePoint p;
   const int64_t col = g * G + threadIdx.x;
-  const bool in = threadIdx.x < G && col < a.nc;
+  bool in = threadIdx.x < G && col < a.nc;
   float x[3] = {0.f, 0.f, 0.f}, lo[3], hi[3];
+  bool far = false;   // at infinity, or there once scaled
   if (in)
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       x[k] = a.xc[col * a.xc_stride + k];
-      if (!finite_bits(x[k])) flag |= kBadValue;
+      far = far || !finite_bits(x[k] * a.coord_scale);
     }
+  const uint64_t far_cols = __ballot(far);
+  if (lane < 2 && threadIdx.x < G) sh.point[2 * wave + lane] = (uint32_t)(far_cols >> (32 * lane));
+  in = in && !far;
   p = lattice_point(a, x, c);
-  if (in && !p.ok) flag |= kOffLattice;
+  const bool off = in && !p.ok;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const float t = (float)lattice_coord(a, x[k], c[k]);
@@ -196,49 +225,100 @@ __device__ __forceinline__ void split16_group(const GammaLaunch& a, int kernel, 
       lo[k] = fminf(lo[k], __shfl_xor(lo[k], o));
       hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], o));
     }
-  if ((threadIdx.x & 63) == 0)
+  if (lane == 0)
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      s_b[threadIdx.x >> 6][k] = lo[k];
-      s_b[threadIdx.x >> 6][4 + k] = hi[k];
+      sh.b[wave][k] = lo[k];
+      sh.b[wave][4 + k] = hi[k];
     }
   __syncthreads();
-  if (flag) atomicOr(s_flag, flag);
+  if (off) atomicOr(&sh.flag, (int)kOffLattice);
 #pragma unroll
   for (int q = 0; q < PARTS; ++q) m = fmaxf(m, s_m[q][j]);
   int ex = 0;
-  if (m > 0.f && finite_bits(m)) (void)__builtin_frexpf(m, &ex);   // m in [2^(ex-1), 2^ex)
-  const int up = 15 - ex;                                             // |y| 2^up < 2^15
+  if (m > 0.f) (void)__builtin_frexpf(m, &ex);   // m in [2^(ex-1), 2^ex)
+  const int up = m > 0.f ? 15 - ex : kNoScale;                        // |y| 2^up < 2^15
   if (part == 0) {
     s_up[j] = (float)up;
     a.yup[g * B + j] = (float)up;
   }
-  __syncthreads();
-  const bool bad = (*s_flag & kBadValue) != 0;   // its columns are added by the product's slow loop instead
-  if (threadIdx.x == 0) {
-    float* b = a.gbox + 8 * g;
+  // columns with a value that the parts do not hold: not finite, or below 2^-22
+  // of the largest (2^-7 where FP16's last place is 2^-24: 2^-18 off); vectors
+  // with such values, or zeros; columns that are not zero.  Most waves have none
+  // of the odd ones.
+  const float low = m > 0.f ? __builtin_ldexpf(1.f, ex - 22) : 0.f;
+  uint32_t bad = 0, nz = ~0u;
+  if (__any(least < __builtin_bit_cast(uint32_t, low) || least == 0 || most >= 0x7f800000u)) {
+    nz = 0;
+    bool gap = m == 0.f;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      float l = s_b[0][k], h = s_b[0][4 + k];
+    for (int u = 0; u < CPT; ++u) {
+      const bool some = y[u] != 0.f, small = __builtin_fabsf(y[u]) < low;
+      if (some) nz |= 1u << u;
+      if (some && (small || !finite_bits(y[u]))) bad |= 1u << u;
+      gap = gap || (small && c0 + u < a.nc);
+    }
+    if (gap && j < a.nv) atomicOr(&sh.gap[j / 32], 1u << (j % 32));
+    bad <<= bit0;
+    nz <<= bit0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      bad |= __shfl_xor(bad, o);
+      nz |= __shfl_xor(nz, o);
+    }
+  }
+  if (lane == 0) {
+    sh.bad[wave] = bad;
+    sh.nz[wave] = nz;
+  }
+  __syncthreads();
+  int count = 0;
+#pragma unroll
+  for (int w = 0; w < G / 32; ++w) count += __builtin_popcount(sh.nz[w]);
+  const bool few = count <= kFewColumns;
+  auto exact_word = [&](int w) { return sh.bad[w] | sh.point[w] | (few ? sh.nz[w] : 0u); };
+  if (threadIdx.x < G / 32) a.gmask[g * (G / 32) + threadIdx.x] = exact_word(threadIdx.x);
+  if (threadIdx.x < 2) a.ggap[2 * g + threadIdx.x] = sh.gap[threadIdx.x];
+  if (wave == kPreThreads / 64 - 1) {   // box, flags and largest entry (rounded down to a power of two); a wave without points
+    int marks = lane < G / 32 ? __builtin_popcount(exact_word(lane & (G / 32 - 1))) : 0;
+#pragma unroll
+    for (int o = 1; o < G / 32; o <<= 1) marks += __shfl_xor(marks, o);   // (lane 3 has them)
+    float size = few || up == kNoScale ? 0.f : __builtin_ldexpf(1.f, 14 - up);   // (lane: vector lane % B)
+#pragma unroll
+    for (int o = 1; o < B; o <<= 1) size = fmaxf(size, __shfl_xor(size, o));
+    const int flags = sh.flag | ((sh.gap[0] | sh.gap[1]) != 0 ? (int)kGaps : 0) | marks * kMarks;
+    float* b = a.gbox + 8 * g;
+    if (lane < 3) {
+      float l = sh.b[0][lane], h = sh.b[0][4 + lane];
 #pragma unroll
       for (int w = 1; w < G / 64; ++w) {
-        l = fminf(l, s_b[w][k]);
-        h = fmaxf(h, s_b[w][4 + k]);
+        l = fminf(l, sh.b[w][lane]);
+        h = fmaxf(h, sh.b[w][4 + lane]);
       }
-      b[k] = bad ? -1e30f : l;
-      b[4 + k] = bad ? 1e30f : h;
+      // A row's distance from the box has to be a lower bound of its distances
+      // from the columns as the product forms them.  Box and row are rounded at
+      // their size relative to the launch's centre (once each), the two
+      // coordinates of a difference relative to the row block's (twice each),
+      // which is no further from a row than zero or 32 units (row_centre).  With
+      // a row as far off as the box that is 6 of 2^-24, taken as 8; what a row
+      // further off adds is 2^-21 of the distance, inside the product's 0.999.
+      const float ck = (float)(lane == 0 ? c[0] : (lane == 1 ? c[1] : c[2]));
+      const float wide = 0x1p-21f * (fmaxf(__builtin_fabsf(l), __builtin_fabsf(h)) + __builtin_fabsf(ck) + 32.f);
+      b[lane] = l <= h ? l - wide : l;
+      b[4 + lane] = l <= h ? h + wide : h;
+    } else if (lane == 3) {
+      b[3] = (float)flags;
+      b[7] = size;
     }
-    b[3] = (float)*s_flag;
-    b[7] = 0.f;
   }
   if (kernel == KA_GAUSSIAN && threadIdx.x < G) {
     // fragment (ks, half), lane 16 q + m of the column's tile
     const int cg = threadIdx.x, ct = cg & 31, vec = cg & 63;
     uint4* dst = a.xs + (g * GT + cg / kCT) * kXEntries + (((cg & 63) >> 5) * 2 + ((ct >> 2) & 1)) * 64 +
                  4 * (ct >> 3) + (ct & 3);
-    // (a column that is none, or of a group that is not finite, is put so far
-    // off that Gamma is zero whatever the row's scale)
-    const float n = bad || !in ? -30000.f : -(p.h[0] * p.h[0] + p.h[1] * p.h[1] + p.h[2] * p.h[2]);
+    // (a column that is none, or is at infinity, is put so far off that Gamma is
+    // zero whatever the row's scale)
+    const float n = !in ? -30000.f : -(p.h[0] * p.h[0] + p.h[1] * p.h[1] + p.h[2] * p.h[2]);
     // the last slot meets a zero of the rows' operand: it carries the scale of vector `vec`
     dst[0] = make_uint4(pack_h2(p.h[0], p.h[1]), pack_h2(p.h[2], n), pack_h2(n - half_of(n), 1.f),
                         pack_h2(1.f, vec < B ? s_up[vec] : 0.f));
@@ -250,14 +330,17 @@ __device__ __forceinline__ void split16_group(const GammaLaunch& a, int kernel, 
                                      pack_h2(b1, b1 - half_of(b1)));
     }
   }
+  if (const uint32_t exact = exact_word(wave) >> bit0)
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) y[u] = exact >> u & 1 ? 0.f : y[u];
 #pragma unroll
   for (int v = 0; v < CPT / 8; ++v) {
     const int cg = part * CPT + 8 * v;        // in the group
     uint32_t h[4], l[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const float y0 = bad ? 0.f : __builtin_ldexpf(y[8 * v + 2 * u], up);
-      const float y1 = bad ? 0.f : __builtin_ldexpf(y[8 * v + 2 * u + 1], up);
+      const int e = 8 * v + 2 * u;
+      const float y0 = __builtin_ldexpf(y[e], up), y1 = __builtin_ldexpf(y[e + 1], up);
       h[u] = pack_h2(y0, y1);
       l[u] = pack_h2(y0 - half_of(y0), y1 - half_of(y1));
     }
@@ -272,9 +355,8 @@ template <int B>
 __global__ __launch_bounds__(kPreThreads) void gamma_split16_kernel(GammaLaunch a, int kernel) {
   __shared__ float s_m[kPreThreads / B][B];
   __shared__ float s_up[B];
-  __shared__ float s_b[kPreThreads / 64][8];
-  __shared__ int s_flag;
-  split16_group<B>(a, kernel, blockIdx.x, s_m, s_up, &s_flag, s_b);
+  __shared__ SplitShared sh;
+  split16_group<B>(a, kernel, blockIdx.x, s_m, s_up, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -322,6 +404,153 @@ __device__ __forceinline__ float centred(const GammaLaunch& a, float x, float c)
   return __builtin_fmaf(x, a.coord_scale_lo, __builtin_fmaf(x, a.coord_scale, -c));
 }
 
+// ---------------------------------------------------------------------------
+// columns and rows in FP32
+//
+// What FP16 parts do not hold is formed as FP32 values, contracted by FP32 MFMAs
+// and added to FP64 totals every 128 columns.  Exponents come from differences
+// of FP64 coordinates, rounded once: no centre has to be chosen, and a pair costs
+// six FP64 operations and a conversion where FP32 with as much accuracy would
+// take twice as many.  All of 85,184^2 at b = 64 takes 11.7 ms so (11.4
+// exponential), 8.0 in the FP32 tiles of gamma.hip with their rounding of
+// coordinates, and 2.8 in FP16 parts; b = 16 5.2, 2.9 and 1.5 ms.  Blocks without
+// such values pay for the look-out: 12,167^2 at b = 16 62.8 -> 66.2 us, 6,500^2 at
+// b = 64 53.5 -> 57.9, 70,000^2 at b = 32 exponential 1.77 -> 1.80 ms, 287,496^2 at
+// b = 64 32.0 -> 32.1 ms.
+// ---------------------------------------------------------------------------
+template <int KERNEL>
+__device__ __forceinline__ float exact_value(const double (&x)[3], const double (&y)[3]) {
+  const double dx = x[0] - y[0], dy = x[1] - y[1], dz = x[2] - y[2];
+  const double e = KERNEL == KA_GAUSSIAN ? __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx)) : (fabs(dx) + fabs(dy)) + fabs(dz);
+  return __builtin_amdgcn_exp2f((float)-e);
+}
+
+__device__ __forceinline__ void exact_point(const GammaLaunch& a, const float* p, double (&x)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] = lattice_coord(a, p[k], 0.0);
+}
+
+// The n columns column(0), column(1), ... against RB groups of 16 rows, added to
+// `tot`; sixteen at a time, the operands of the next sixteen or 32 on their way.
+template <int KERNEL, int B, int RB, class Column>
+__device__ __forceinline__ void exact_columns(const GammaLaunch& a, const double (&x)[RB][3], int n, Column column,
+                                              d4v (&tot)[RB][B / 16]) {
+  constexpr int NT = B / 16;
+  const int q = (threadIdx.x & 63) >> 4, l16 = threadIdx.x & 15;
+  float p[2][4][3], y[2][4][NT];
+  auto load = [&](int i0, float (&lp)[4][3], float (&ly)[4][NT]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int i = i0 + 4 * s + q;
+      const int64_t c = column(i < n ? i : n - 1);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) lp[s][k] = a.xc[c * a.xc_stride + k];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) ly[s][t] = a.Y[c * B + 16 * t + l16];
+    }
+  };
+  f4v acc[RB][NT];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[rb][t] = (f4v){0.f, 0.f, 0.f, 0.f};
+  auto work = [&](int i0, const float (&wp)[4][3], const float (&wy)[4][NT]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool on = i0 + 4 * s + q < n;
+      double z[3];
+      exact_point(a, wp[s], z);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const float e = on ? exact_value<KERNEL>(x[rb], z) : 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[rb][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(e, on ? wy[s][t] : 0.f, acc[rb][t], 0, 0, 0);
+      }
+    }
+  };
+  if (n <= 0) return;
+  load(0, p[0], y[0]);
+  load(16, p[1], y[1]);
+  for (int i0 = 0; i0 < n; i0 += 32) {
+    work(i0, p[0], y[0]);
+    load(i0 + 32, p[0], y[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    work(i0 + 16, p[1], y[1]);
+    load(i0 + 48, p[1], y[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if ((i0 & 127) == 96 || i0 + 32 >= n)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          tot[rb][t] += __builtin_convertvector(acc[rb][t], d4v);
+          acc[rb][t] = (f4v){0.f, 0.f, 0.f, 0.f};
+        }
+  }
+}
+
+__device__ __forceinline__ double row_factor(const GammaLaunch& a, int64_t row) {
+  return (double)(a.out_scale * (a.rs ? a.rs[row] : 1.0f));
+}
+
+// Adds the columns of [c_begin, c_end) that are marked in a.gmask to `tot`: as a
+// rule a few (of N(0, 1) blocks one in 80,000 at b = 16), listed in s_few in any
+// order; else they are gathered in their order from up to 8192 columns at a time.
+constexpr int kFewMarks = 64;
+constexpr int kListColumns = 32 * kThreads;
+static_assert(sizeof(uint16_t) * kListColumns <= sizeof(uint4) * kXRing * kXEntries, "the list takes the operands' place in LDS");
+
+template <int KERNEL, int B, int RB>
+__device__ __forceinline__ void add_marked_columns(const GammaLaunch& a, int64_t row0, int64_t c_begin, int64_t c_end,
+                                                   const int* s_few, int n_few, void* s_list, int* s_cnt,
+                                                   d4v (&tot)[RB][B / 16]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double x[RB][3];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int64_t r = row0 + 16 * rb + (lane & 15);
+    exact_point(a, a.xr + (r < a.nr ? r : a.nr - 1) * a.xr_stride, x[rb]);
+  }
+  if (n_few <= kFewMarks) {
+    int* list = reinterpret_cast<int*>(s_list);
+    if ((int)threadIdx.x < n_few) {   // sorted, so that sums don't depend on the order of arrival
+      const int v = s_few[threadIdx.x];
+      int at = 0;
+      for (int k = 0; k < n_few; ++k) at += s_few[k] < v;
+      list[at] = v;
+    }
+    __syncthreads();
+    exact_columns<KERNEL, B, RB>(a, x, n_few, [&](int i) { return c_begin + list[i]; }, tot);
+    return;
+  }
+  uint16_t* list = reinterpret_cast<uint16_t*>(s_list);
+  for (int64_t cb = c_begin; cb < c_end; cb += kListColumns) {
+    // a word of 32 columns per thread (splits start at whole words, and no
+    // column past the last is marked)
+    uint32_t w = cb + 32 * (int)threadIdx.x < c_end ? a.gmask[cb / 32 + threadIdx.x] : 0u;
+    const int own = __builtin_popcount(w);
+    int k = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(k, o);
+      if (lane >= o) k += v;
+    }
+    __syncthreads();   // the list and counts of the columns before have been read
+    if (lane == 63) s_cnt[wave] = k;
+    __syncthreads();
+    int at = k - own, n = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (v < wave) at += s_cnt[v];
+      n += s_cnt[v];
+    }
+    for (; w; w &= w - 1) list[at++] = (uint16_t)(32 * threadIdx.x + __builtin_ctz(w));
+    __syncthreads();
+    exact_columns<KERNEL, B, RB>(a, x, n, [&](int i) { return cb + list[i]; }, tot);
+  }
+}
+
 // Centre of a workgroup's rows along direction k for the difference form: the
 // middle of their box, or zero where that would cost a row accuracy.  A
 // coordinate is rounded at its distance from the centre, half the box's extent
@@ -341,8 +570,9 @@ __device__ __forceinline__ float row_centre(const float (*s_box)[8], int k, floa
 template <int KERNEL, int B, int RB, bool GRAM>
 __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rblk, int split,
                                                uint4 (*s_x)[kXEntries], uint4 (*s_y)[2 * h16_entries<B>()],
-                                               float c0, float c1, float c2, const double (&cl)[3], int flags,
-                                               const float (*s_row)[64 * RB], float (*s_inv)[64 * RB]) {
+                                               float c0, float c1, float c2, const double (&cl)[3],
+                                               const float (*s_row)[64 * RB], float (*s_inv)[64 * RB],
+                                               const int* s_few, int marks, int* s_cnt, d4v (&tot)[RB][B / 16]) {
   constexpr int NT = B / 16;
   constexpr int KS = kCT / 32;
   constexpr int S = KS * RB;                 // steps per tile: 16 rows x 32 columns each
@@ -355,6 +585,15 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
   const int64_t row0 = rblk * ROWS + wave * 16 * RB;
   const int64_t c_begin = (int64_t)split * a.cols_per_split;
   const int64_t c_end = (c_begin + a.cols_per_split < a.nc) ? c_begin + a.cols_per_split : a.nc;
+
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) tot[rb][t] = (d4v){0.0, 0.0, 0.0, 0.0};
+  if (marks > 0) {
+    add_marked_columns<KERNEL, B, RB>(a, row0, c_begin, c_end, s_few, marks, &s_x[0][0], s_cnt, tot);
+    __syncthreads();   // the list has been read
+  }
 
   // rows: Gram operand and factor, or centred coordinates
   h8v bx[RB];
@@ -396,17 +635,9 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
   // to 2^15; the inverse goes to s_inv for the sums of the group (`par` its
   // parity).  Row points are read from LDS: this runs once per group.
   // The distance must not come out larger than the kernel's exponents have it,
-  // or Gamma passes 2^16.  Box and row are rounded to FP32 relative to the
-  // launch's centre, the exponents' coordinates relative to the workgroup's.  On
-  // the lattice (below 31 units) that is nothing next to the factor of two in
-  // hand; differences may be of any size, and there each gap is shortened by the
-  // roundings it can hold: one of row and box, two each of the coordinates in a
-  // difference, 6 of 2^-24, taken as 8.
+  // or Gamma passes 2^16: the pre-pass widens the boxes by what roundings can do.
   float Sg[RB];
   float gb[6];   // box of the next group
-  const float off[3] = {uniform(__builtin_fabsf((float)cl[0]) + __builtin_fabsf(c0)),
-                        uniform(__builtin_fabsf((float)cl[1]) + __builtin_fabsf(c1)),
-                        uniform(__builtin_fabsf((float)cl[2]) + __builtin_fabsf(c2))};
   auto load_box = [&](int64_t g) {
     const uniform_float* b = (const uniform_float*)(uintptr_t)(a.gbox + 8 * (g < a.ngroups ? g : 0));
 #pragma unroll
@@ -422,13 +653,7 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
       float d = 0.f;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        const float x = s_row[k][r];
-        float gap = fmaxf(gb[k] - x, x - gb[3 + k]);
-        if constexpr (!GRAM) {
-          const float far = fmaxf(__builtin_fabsf(x), fmaxf(__builtin_fabsf(gb[k]), __builtin_fabsf(gb[3 + k])));
-          gap -= 0x1p-21f * (far + off[k]);
-        }
-        gap = fmaxf(gap, 0.f);
+        const float x = s_row[k][r], gap = fmaxf(fmaxf(gb[k] - x, x - gb[3 + k]), 0.f);
         d += KERNEL == KA_GAUSSIAN ? gap * gap : gap;
       }
       const int up = 15 + (int)fminf(0.999f * d, 110.f);
@@ -440,15 +665,13 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
   row_scales(0);
 
   const f4v zero4 = {0.f, 0.f, 0.f, 0.f};
-  f4v acc[RB][NT], accx[RB][NT];
-  d4v tot[RB][NT];
+  f4v acc[RB][NT], accx[RB][NT];   // (tot comes with the columns that are added in FP32)
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       acc[rb][t] = zero4;
       accx[rb][t] = zero4;
-      tot[rb][t] = (d4v){0.0, 0.0, 0.0, 0.0};
     }
 
   const int64_t ntile = (c_end - c_begin + kCT - 1) / kCT;
@@ -484,7 +707,7 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
       float t = raw;
       if (wave < 3) {
         t = centred(a, raw, cw);
-        if (!finite_bits(t)) t = 1e18f;        // Gamma = 0 here; its group is added by the slow loop
+        if (!finite_bits(t)) t = 1e18f;        // Gamma = 0 here: the column is added in FP32
       }
       reinterpret_cast<float*>(&s_x[slot][0])[wave * kCT + lane] = t;
     }
@@ -661,44 +884,371 @@ __device__ __forceinline__ void gamma_h16_tile(const GammaLaunch& a, int64_t rbl
     xc = xn;
   }
   __builtin_amdgcn_s_waitcnt(kVm0);   // no load to LDS outlives the tile loop
+}
 
-  // Groups with a value that is not finite in Y or in the points: their
-  // operands are zero above, and they are added here as they stand, one pair
-  // at a time, so that infinities and NaN come out as from FP32 products.
-  if (flags & kBadValue) {
-    for (int64_t g = c_begin / G; g * G < c_end; ++g) {
-      if (((int)a.gbox[8 * g + 3] & kBadValue) == 0) continue;
-      for (int64_t c = g * G > c_begin ? g * G : c_begin; c < (g + 1) * G && c < c_end; ++c) {
-        const float* y = a.xc + c * a.xc_stride;
+// the sum of s over the workgroup, in every thread
+__device__ __forceinline__ double block_sum(double s, double* s_sum) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  __syncthreads();   // the sums before have been read
+  if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = s;
+  __syncthreads();
+  return (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+}
+
+// Which stored results may have lost what matters: entries (i B + vector, i the
+// row's place) into s_entry, whole rows into s_list.  A low result is not
+// cancellation if no vector of the row comes out larger for its size (a hole
+// between scattered columns): the row.  In a vector with zeros or very small
+// entries the near columns may be among these: the entry, unless the group that
+// could give most holds enough of |Gamma| |Y|; the rows, if the entries are many.
+// (N(0, 1) blocks of 287,496 x 64: a dozen entries in 50 row blocks get as far
+// as the check of the group, none further.)
+constexpr float kLostCut = 0x1p-19f;
+constexpr int kEntries = 64;
+
+struct Lossy {
+  int rows, entries;
+};
+
+template <int B>
+struct LossyShared {
+  float size[kThreads];       // largest entry of vector t % B, over part of the groups, then [0 .. B) over all
+  uint32_t gap[kThreads];     // whether it has zeros or very small entries
+  uint32_t rows[8], some[8];  // a bit per row; of rows with entries
+  double sum[4];
+  int n;
+};
+
+template <int KERNEL, int B, int RB>
+__device__ __forceinline__ Lossy lossy_results(const GammaLaunch& a, int64_t row0, int64_t c_begin, int64_t c_end,
+                                               int64_t g0, int64_t g1, const float* out, const float* s_lost,
+                                               const int* s_best, LossyShared<B>& sh, uint16_t* s_list,
+                                               uint16_t* s_entry) {
+  constexpr int NT = B / 16, ROWS = 64 * RB;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, l16 = lane & 15;
+  float v_size = 0.f;
+  uint32_t v_gap = 0;
+  for (int64_t g = g0 + threadIdx.x / B; g < g1 && g < a.ngroups; g += kThreads / B) {
+    const int vec = threadIdx.x % B, up = (int)a.yup[g * B + vec];
+    if (up != kNoScale) v_size = fmaxf(v_size, __builtin_ldexpf(1.f, 14 - up));
+    v_gap |= a.ggap[2 * g + vec / 32] >> (vec % 32) & 1;
+  }
+  sh.size[threadIdx.x] = v_size;
+  sh.gap[threadIdx.x] = v_gap;
+  if (threadIdx.x < 8) sh.rows[threadIdx.x] = sh.some[threadIdx.x] = 0;
+  if (threadIdx.x == 0) sh.n = 0;
+  __syncthreads();
+  if (threadIdx.x < B)
+    for (int v = threadIdx.x + B; v < kThreads; v += B) {
+      v_size = fmaxf(v_size, sh.size[v]);
+      v_gap |= sh.gap[v];
+    }
+  __syncthreads();
+  if (threadIdx.x < B) {
+    sh.size[threadIdx.x] = v_size;
+    sh.gap[threadIdx.x] = v_gap;
+  }
+  __syncthreads();
+  float largest = 0.f;
+  for (int v = 0; v < B; ++v) largest = fmaxf(largest, sh.size[v]);
+  float size[NT];   // of vectors 16 t + l16, the largest 1
+  bool gap[NT];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int64_t row = row0 + 16 * rb + 4 * q + r;
-            const float* x = a.xr + (row < a.nr ? row : a.nr - 1) * a.xr_stride;
-            const float k = __builtin_amdgcn_exp2f(-pair_exponent<KERNEL>(
-                x[0] * a.coord_scale - y[0] * a.coord_scale, x[1] * a.coord_scale - y[1] * a.coord_scale,
-                x[2] * a.coord_scale - y[2] * a.coord_scale));
+  for (int t = 0; t < NT; ++t) {
+    size[t] = largest > 0.f ? sh.size[16 * t + l16] / largest : 0.f;
+    gap[t] = sh.gap[16 * t + l16] != 0;
+  }
+  for (int k = 0; k < 4 * RB; ++k) {
+    const int i = wave * 16 * RB + 16 * (k / 4) + 4 * q + k % 4;
+    const bool in = row0 + i < a.nr;
+    const int64_t row = in ? row0 + i : a.nr - 1;
+    const double lost = in ? fabs(row_factor(a, row)) * (double)(kLostCut * s_lost[i]) : 0.0;
+    bool low[NT], all = lost > 0.0;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) tot[rb][t][r] += (double)(k * a.Y[c * B + 16 * t + (lane & 15)]);
-          }
+    for (int t = 0; t < NT; ++t) {
+      low[t] = fabs((double)out[row * B + 16 * t + l16]) < lost * (double)size[t];
+      all = all && (low[t] || size[t] == 0.f);
+    }
+    const bool whole = (__ballot(all) >> (16 * q) & 0xffff) == 0xffff;
+    if (whole && l16 == 0) atomicOr(&sh.rows[i / 32], 1u << (i % 32));
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (low[t] && gap[t] && !whole) {
+        const int at = atomicAdd(&sh.n, 1);
+        if (at < kEntries) s_entry[at] = (uint16_t)(i * B + 16 * t + l16);
+        atomicOr(&sh.some[i / 32], 1u << (i % 32));
       }
+  }
+  __syncthreads();
+  const int found = sh.n;
+  const bool many = found > kEntries;
+  Lossy n = {0, 0};
+  for (int k = 0; k < (many ? 0 : found); ++k) {
+    const int e = s_entry[k], i = e / B, vec = e % B;
+    const int64_t c = (g0 + s_best[i]) * kGroup + threadIdx.x;
+    double s = 0.0, x[3], z[3];
+    exact_point(a, a.xr + (row0 + i) * a.xr_stride, x);
+#pragma unroll
+    for (int u = 0; u < kGroup / kThreads; ++u) {
+      const int64_t cu = c + u * kThreads;
+      if (cu < c_begin || cu >= c_end) continue;
+      exact_point(a, a.xc + cu * a.xc_stride, z);
+      s += (double)(exact_value<KERNEL>(x, z) * __builtin_fabsf(a.Y[cu * B + vec]));
+    }
+    s = block_sum(s, sh.sum);
+    if (!(s >= (double)(kLostCut * s_lost[i]) * (double)(sh.size[vec] / largest))) {
+      if (threadIdx.x == 0) s_entry[n.entries] = (uint16_t)e;   // (n.entries <= k, and all have read entry k)
+      ++n.entries;
     }
   }
+  int at = 0;
+  uint32_t own = 0;
+  for (int w = 0; w < ROWS / 32; ++w) {
+    const uint32_t word = sh.rows[w] | (many ? sh.some[w] : 0u);
+    if (w < (int)threadIdx.x / 32) at += __builtin_popcount(word);
+    if (w == (int)threadIdx.x / 32) own = word;
+    n.rows += __builtin_popcount(word);
+  }
+  const uint32_t bit = threadIdx.x % 32;
+  if (own >> bit & 1) s_list[at + __builtin_popcount(own & ((1u << bit) - 1))] = (uint16_t)threadIdx.x;
+  __syncthreads();   // (also: what is done again has been written)
+  return n;
+}
 
-  float* out = a.nsplit > 1 ? a.partial + (size_t)split * a.nr * B : a.Z;
+// Rows row0 + s_list[0 .. n) again, all columns of [c_begin, c_end) in FP32:
+// 16 rows at a time, a quarter of the columns per wave.
+template <int KERNEL, int B>
+__device__ __forceinline__ void redo_rows(const GammaLaunch& a, int64_t row0, const uint16_t* s_list, int n,
+                                          int64_t c_begin, int64_t c_end, double (*s_sum)[16 * B], float* out) {
+  constexpr int NT = B / 16;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i0 = 0; i0 < n; i0 += 16) {
+    const int i = i0 + (lane & 15);
+    double x[1][3];
+    exact_point(a, a.xr + (row0 + s_list[i < n ? i : n - 1]) * a.xr_stride, x[0]);
+    d4v tot[1][NT];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
+    for (int t = 0; t < NT; ++t) tot[0][t] = (d4v){0.0, 0.0, 0.0, 0.0};
+    const int64_t part = (c_end - c_begin + 3) / 4, c0 = c_begin + wave * part;
+    exact_columns<KERNEL, B, 1>(a, x, (int)(c_end - c0 < part ? c_end - c0 : part), [&](int k) { return c0 + k; }, tot);
+    __syncthreads();   // the sums of the rows before have been read
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_sum[wave][(4 * (lane >> 4) + r) * B + 16 * t + (lane & 15)] = tot[0][t][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * B; e += kThreads)
+      if (i0 + e / B < n) {
+        const int64_t row = row0 + s_list[i0 + e / B];
+        out[row * B + e % B] = (float)(row_factor(a, row) * ((s_sum[0][e] + s_sum[1][e]) + (s_sum[2][e] + s_sum[3][e])));
+      }
+  }
+}
+
+// One entry again: a column per thread at a time, eight on their way.
+template <int KERNEL, int B>
+__device__ __forceinline__ void redo_entry(const GammaLaunch& a, int64_t row, int vec, int64_t c_begin, int64_t c_end,
+                                           double* s_sum, float* out) {
+  double x[3], s = 0.0;
+  exact_point(a, a.xr + row * a.xr_stride, x);
+  for (int64_t cb = c_begin; cb < c_end; cb += 8 * kThreads) {
+    float p[8][3], y[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t c = cb + u * kThreads + threadIdx.x, cc = c < c_end ? c : c_end - 1;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) p[u][k] = a.xc[cc * a.xc_stride + k];
+      y[u] = a.Y[cc * B + vec];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      double z[3];
+      exact_point(a, p[u], z);
+      const float e = exact_value<KERNEL>(x, z);
+      if (cb + u * kThreads + threadIdx.x < c_end) s += (double)e * (double)y[u];
+    }
+  }
+  s = block_sum(s, s_sum);
+  if (threadIdx.x == 0) out[row * B + vec] = (float)(row_factor(a, row) * s);
+}
+
+// One work item.  False where it has to be formed in FP32 as a whole: half of its
+// columns or more are marked (not begun), or a quarter of its rows to be done
+// again.
+template <int KERNEL, int B, int RB>
+__device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rblk, int split, uint4 (*s_x)[kXEntries],
+                                               uint4 (*s_y)[2 * h16_entries<B>()], float (*s_box)[8]) {
+  constexpr int ROWS = 64 * RB;
+  __shared__ float s_row[3][ROWS];
+  __shared__ float s_inv[2][ROWS];
+  __shared__ float s_lost[ROWS];
+  __shared__ int s_best[ROWS];
+  __shared__ int s_flags, s_marks, s_size, s_cnt[4], s_few[kFewMarks];
+  if (threadIdx.x == 0) s_flags = s_marks = s_size = 0;   // (gram_rows has a barrier)
+  double cl[3];
+  launch_centre(a, cl);
+  float c0, c1, c2;
+  (void)gram_rows<RB>(a, rblk, s_box, c0, c1, c2);
+  c0 = uniform(row_centre<KERNEL>(s_box, 0, c0));
+  c1 = uniform(row_centre<KERNEL>(s_box, 1, c1));
+  c2 = uniform(row_centre<KERNEL>(s_box, 2, c2));
+  const int64_t row0 = rblk * ROWS;
+  const int64_t c0s = (int64_t)split * a.cols_per_split;
+  const int64_t c1s = c0s + a.cols_per_split < a.nc ? c0s + a.cols_per_split : a.nc;
+  const int64_t g0 = c0s / kGroup, g1 = (c1s + kGroup - 1) / kGroup;
+  // the flags of the columns' groups, their marked columns and the largest size of
+  // Y (the row's point is on its way meanwhile)
+  const int64_t own = row0 + threadIdx.x % ROWS;
+  const float* xr = a.xr + (own < a.nr ? own : a.nr - 1) * a.xr_stride;
+  const float x[3] = {xr[0], xr[1], xr[2]};
+  int flags = 0, size = 0;
+  for (int64_t g = g0 + threadIdx.x; g < g1; g += kThreads) {
+    const int f = (int)a.gbox[8 * g + 3];
+    flags |= f & (kMarks - 1);
+    size = max(size, __builtin_bit_cast(int, a.gbox[8 * g + 7]));   // (not negative: in order as integers too)
+    if (f > kMarks * kFewMarks) {
+      atomicAdd(&s_marks, f / kMarks);
+    } else if (f >= kMarks) {
+      for (int k = 0; k < kGroup / 32; ++k)
+        for (uint32_t w = a.gmask[g * (kGroup / 32) + k]; w; w &= w - 1) {
+          const int64_t c = g * kGroup + 32 * k + __builtin_ctz(w);
+          if (c < c0s || c >= c1s) continue;
+          const int at = atomicAdd(&s_marks, 1);
+          if (at < kFewMarks) s_few[at] = (int)(c - c0s);
+        }
+    }
+  }
+  // the rows' points relative to the launch's centre, and whether they are on the
+  // lattice
+  if (threadIdx.x < ROWS) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s_row[k][threadIdx.x] = (float)lattice_coord(a, x[k], cl[k]);
+    if (KERNEL == KA_GAUSSIAN && !lattice_point(a, x, cl).ok) flags |= kOffLattice;
+  }
+  if (size) atomicMax(&s_size, size);
+  if (flags) atomicOr(&s_flags, flags);
+  __syncthreads();
+  flags = __builtin_amdgcn_readfirstlane(s_flags);
+  const int marks = __builtin_amdgcn_readfirstlane(s_marks);
+  if (2 * (int64_t)marks >= c1s - c0s) return false;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4;
+  d4v tot[RB][B / 16];
+  if (KERNEL == KA_GAUSSIAN && !(flags & kOffLattice))
+    gamma_h16_tile<KERNEL, B, RB, true>(a, rblk, split, s_x, s_y, c0, c1, c2, cl, s_row, s_inv, s_few, marks, s_cnt, tot);
+  else
+    gamma_h16_tile<KERNEL, B, RB, false>(a, rblk, split, s_x, s_y, c0, c1, c2, cl, s_row, s_inv, s_few, marks, s_cnt, tot);
+
+  // A kernel value is good to 2^-40 of what it could be at the row's distance
+  // from the box of its group.  s_lost has the sum over the groups of what they
+  // could give; each pair's loss is 2^-40 of that, all of a row's, with random
+  // roundings, 2^-38, and a result below 2^-19 of it may owe that to columns that
+  // are all much further off than the boxes.  It takes a load or more per group,
+  // so first: is a result low if all groups were at the row?
+  const double largest = (double)(kLostCut * (float)(g1 - g0)) * (double)__builtin_bit_cast(float, s_size);
+  bool low = false;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t row = row0 + 16 * rb + 4 * q + r;
-      if (row < a.nr) {
-        const double f = (double)(a.out_scale * (a.rs ? a.rs[row] : 1.0f));
+      bool all = true;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) out[row * B + 16 * t + (lane & 15)] = (float)(f * tot[rb][t][r]);
+      for (int t = 0; t < B / 16; ++t) all = all && fabs(tot[rb][t][r]) < largest;
+      low = low || all;
+    }
+  const bool look = __syncthreads_or(low || (flags & kGaps)) != 0;
+  if (look) {
+    if (threadIdx.x < ROWS) {
+      float x[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) x[k] = s_row[k][threadIdx.x];
+      float lost = 0.f, most = 0.f;
+      int best = 0;
+#pragma unroll 4
+      for (int64_t g = g0; g < g1; ++g) {
+        const uniform_float* b = (const uniform_float*)(uintptr_t)(a.gbox + 8 * g);
+        float d = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const float gap = fmaxf(fmaxf(b[k] - x[k], x[k] - b[4 + k]), 0.f);
+          d += KERNEL == KA_GAUSSIAN ? gap * gap : gap;
+        }
+        const float v = __builtin_amdgcn_exp2f(-d) * b[7];
+        lost += v;
+        if (v > most) {
+          most = v;
+          best = (int)(g - g0);
+        }
       }
+      s_lost[threadIdx.x] = lost;
+      s_best[threadIdx.x] = best;
+    }
+    __syncthreads();
+  }
+  float* out = a.nsplit > 1 ? a.partial + (size_t)split * a.nr * B : a.Z;
+  bool some = false, whole = false;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int r0 = wave * 16 * RB + 16 * rb + 4 * q;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = row0 + r0 + r;
+      bool all = row < a.nr;
+      if (row < a.nr) {
+        const double f = row_factor(a, row), lost = look ? (double)(kLostCut * s_lost[r0 + r]) : 0.0;
+#pragma unroll
+        for (int t = 0; t < B / 16; ++t) {
+          const bool low = fabs(tot[rb][t][r]) < lost;
+          some = some || low;
+          all = all && low;
+          out[row * B + 16 * t + (lane & 15)] = (float)(f * tot[rb][t][r]);
+        }
+      }
+      whole = whole || (__ballot(all) >> (16 * q) & 0xffff) == 0xffff;
     }
   }
+  if (!look || !__syncthreads_or(whole || (some && (flags & kGaps)))) return true;
+  uint16_t* s_list = reinterpret_cast<uint16_t*>(&s_x[0][0]);
+  constexpr size_t kPlace = sizeof(uint4) * kYRing * 2 * h16_entries<B>();
+  static_assert(sizeof(LossyShared<B>) <= kPlace && sizeof(double) * 64 * B <= kPlace, "both take the place of Y's tiles");
+  const Lossy n = lossy_results<KERNEL, B, RB>(a, row0, c0s, c1s, g0, g1, out, s_lost, s_best,
+                                               *reinterpret_cast<LossyShared<B>*>(&s_y[0][0]), s_list, s_list + ROWS);
+  if (4 * n.rows >= ROWS) return false;
+  if (n.rows > 0)
+    redo_rows<KERNEL, B>(a, row0, s_list, n.rows, c0s, c1s, reinterpret_cast<double(*)[16 * B]>(&s_y[0][0]), out);
+  for (int i = 0; i < n.entries; ++i)
+    redo_entry<KERNEL, B>(a, row0 + s_list[ROWS + i] / B, s_list[ROWS + i] % B, c0s, c1s,
+                          reinterpret_cast<double*>(&s_y[0][0]), out);
+  return true;
+}
+
+// One work item, all of it in FP32.
+template <int KERNEL, int B, int RB>
+__device__ __forceinline__ void exact_item(const GammaLaunch& a, int64_t rblk, int split) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t row0 = (rblk * 4 + wave) * (16 * RB);
+  const int64_t c_begin = (int64_t)split * a.cols_per_split;
+  const int64_t c_end = c_begin + a.cols_per_split < a.nc ? c_begin + a.cols_per_split : a.nc;
+  double x[RB][3];
+  d4v tot[RB][B / 16];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int64_t r = row0 + 16 * rb + (lane & 15);
+    exact_point(a, a.xr + (r < a.nr ? r : a.nr - 1) * a.xr_stride, x[rb]);
+#pragma unroll
+    for (int t = 0; t < B / 16; ++t) tot[rb][t] = (d4v){0.0, 0.0, 0.0, 0.0};
+  }
+  exact_columns<KERNEL, B, RB>(a, x, (int)(c_end - c_begin), [&](int i) { return c_begin + i; }, tot);
+  float* out = a.nsplit > 1 ? a.partial + (size_t)split * a.nr * B : a.Z;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = row0 + 16 * rb + 4 * (lane >> 4) + r;
+      if (row < a.nr)
+#pragma unroll
+        for (int t = 0; t < B / 16; ++t) out[row * B + 16 * t + (lane & 15)] = (float)(row_factor(a, row) * tot[rb][t][r]);
+    }
 }
 
 // Waves per SIMD: as many as the registers allow (b = 16: 165; b = 32 and 64:
@@ -711,49 +1261,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(h16_wa
 void gamma_f16x3_kernel(GammaLaunch a) {
   __shared__ uint4 s_x[kXRing][kXEntries];
   __shared__ uint4 s_y[kYRing][2 * h16_entries<B>()];
-  constexpr int ROWS = 64 * RB;
   __shared__ float s_box[4][8];
-  __shared__ float s_row[3][ROWS];
-  __shared__ float s_inv[2][ROWS];
-  __shared__ int s_flags;
   int64_t rblk;
   int split;
   if (!gamma_item(a, rblk, split)) return;
-  double cl[3];
-  launch_centre(a, cl);
-  float c0, c1, c2;
-  (void)gram_rows<RB>(a, rblk, s_box, c0, c1, c2);
-  c0 = uniform(row_centre<KERNEL>(s_box, 0, c0));
-  c1 = uniform(row_centre<KERNEL>(s_box, 1, c1));
-  c2 = uniform(row_centre<KERNEL>(s_box, 2, c2));
-  // the rows' points relative to the launch's centre, whether they are on the
-  // lattice, and the flags of the columns' groups
-  int flags = 0;
-  for (int r = threadIdx.x; r < ROWS; r += kThreads) {
-    const int64_t row = rblk * ROWS + r;
-    const float* x = a.xr + (row < a.nr ? row : a.nr - 1) * a.xr_stride;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float t = (float)lattice_coord(a, x[k], cl[k]);
-      s_row[k][r] = t;
-    }
-    if (KERNEL == KA_GAUSSIAN && !lattice_point(a, x, cl).ok) flags |= kOffLattice;
-  }
-  const int64_t c0s = (int64_t)split * a.cols_per_split;
-  const int64_t g0 = c0s / kGroup, g1 = (c0s + a.cols_per_split + kGroup - 1) / kGroup;
-  for (int64_t g = g0 + threadIdx.x; g < g1 && g < a.ngroups; g += kThreads) flags |= (int)a.gbox[8 * g + 3];
-  if (threadIdx.x == 0) s_flags = 0;
-  __syncthreads();
-  if (flags) atomicOr(&s_flags, flags);
-  __syncthreads();
-  flags = __builtin_amdgcn_readfirstlane(s_flags);
-  if constexpr (KERNEL == KA_GAUSSIAN) {
-    if (!(flags & kOffLattice)) {
-      gamma_h16_tile<KERNEL, B, RB, true>(a, rblk, split, s_x, s_y, c0, c1, c2, cl, flags, s_row, s_inv);
-      return;
-    }
-  }
-  gamma_h16_tile<KERNEL, B, RB, false>(a, rblk, split, s_x, s_y, c0, c1, c2, cl, flags, s_row, s_inv);
+  if (!gamma_h16_item<KERNEL, B, RB>(a, rblk, split, s_x, s_y, s_box)) exact_item<KERNEL, B, RB>(a, rblk, split);
 }
 
 // ---------------------------------------------------------------------------
@@ -780,10 +1292,10 @@ hipError_t launch_gamma_f16x3(const GammaLaunch& a, int kernel, int b, dim3 grid
   }
 }
 
-// scratch: Y's fragments, the points' operands, the scales, the boxes
+// scratch: Y's fragments, the points' operands, the scales, the boxes, the marks
 size_t gamma_f16x3_bytes(int64_t nc, int b) {
   const size_t ng = ((size_t)nc + kGroup - 1) / kGroup;
-  return ng * (kGroup * (b * 4 + 64) + b * sizeof(float) + 8 * sizeof(float));
+  return ng * (kGroup * (b * 4 + 64) + b * sizeof(float) + 8 * sizeof(float) + kGroup / 8 + 8);
 }
 
 void gamma_f16x3_place(GammaLaunch& a, int b, void* work) {
@@ -796,6 +1308,10 @@ void gamma_f16x3_place(GammaLaunch& a, int b, void* work) {
   a.yup = (float*)p;
   p += ng * b * sizeof(float);
   a.gbox = (float*)p;
+  p += ng * 8 * sizeof(float);
+  a.gmask = (uint32_t*)p;
+  p += ng * (kGroup / 8);
+  a.ggap = (uint32_t*)p;
   a.ngroups = (int64_t)ng;
 }
 

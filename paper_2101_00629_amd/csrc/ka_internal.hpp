@@ -26,7 +26,9 @@ struct GammaLaunch {
   uint4* ys;              // split products: Y as hi/lo BF16 or FP16 MFMA fragments; filled by launch_gamma
   uint4* xs;              // split FP16: Gram operands of the column points; filled by launch_gamma
   float* yup;             // split FP16: scale exponent of each vector in each column group; filled by launch_gamma
-  float* gbox;            // split FP16: bounding box and flag of each column group; filled by launch_gamma
+  float* gbox;            // split FP16: bounding box, flags and size of Y of each column group; filled by launch_gamma
+  uint32_t* gmask;        // split FP16: a bit per column that is added in FP32; filled by launch_gamma
+  uint32_t* ggap;         // split FP16: a bit per vector with zeros or very small entries, 2 words a group; filled by launch_gamma
   int64_t ngroups;        // split FP16: column groups; filled by launch_gamma
   float coord_scale;      // applied to every coordinate on load
   float coord_scale_lo;   // what coord_scale leaves of the FP64 scale (split FP16)

@@ -1,0 +1,92 @@
+"""Large kernel products whose blocks or kernel values span more than FP16 parts
+hold: entries of very different size inside one group of 512 columns, blocks with
+few nonzero rows, and rows none of whose columns is near.
+
+Bar: |Z - Z_ref| <= tol (|Gamma| |Y|) elementwise, with nothing added for the
+largest entries of a group: 1e-5, and where all pairs are far apart the rounding
+of FP32 coordinates on top.  (Gaussian: coordinates up to 15 scaled units are
+2^-21 off, differences 2^-20, an exponent d^2 with d <= 6 twelve times that in
+each of three directions at worst sqrt(3) of it, times ln 2: 1.4e-5.
+Exponential: up to 72 units, 2^-18 a coordinate, 2^-17 a difference, three of
+them, times ln 2: 1.6e-5.)"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2101_00629_amd as K
+from oracle import kernels
+from workloads import normal_block, tensor_grid_points, uniform_points
+
+pytestmark = pytest.mark.gpu
+
+NAMES = {K.KA_GAUSSIAN: "gaussian", K.KA_EXP_L1: "exponential"}
+KERNELS = [K.KA_GAUSSIAN, K.KA_EXP_L1]
+
+
+def _check(kernel, ell, X, C, Y, tol=1e-5, precision=K.KA_FP32):
+    d = dict(dtype=torch.float32, device="cuda")
+    xr, xc, y = torch.tensor(X, **d), torch.tensor(C, **d), torch.tensor(Y, **d)
+    z = torch.full((len(X), Y.shape[1]), float("nan"), **d)
+    nb = K.ka_gamma_workspace(len(X), len(C), Y.shape[1], precision)
+    assert len(X) * len(C) * Y.shape[1] > 4e8 and nb >= len(C) * (4 * Y.shape[1] + 64)   # the split-FP16 route
+    work = torch.full((nb // 4,), float("nan"), **d)
+    K.ka_gamma_apply(kernel, 1.0, ell, xr, xc, y, z, precision, work)
+    Z = z.cpu().numpy().astype(np.float64)
+    G = kernels.kernel_matrix(NAMES[kernel], xr.cpu().numpy().astype(np.float64), xc.cpu().numpy().astype(np.float64),
+                              ell, 1.0)
+    Yd = y.cpu().numpy().astype(np.float64)
+    ref, scale = G @ Yd, np.abs(G) @ np.abs(Yd)
+    ok = scale > 1e-30
+    assert np.isfinite(Z).all() and (np.abs(Z[~ok]) < 1e-29).all()
+    err = np.abs(Z - ref)[ok] / scale[ok]
+    assert err.max() < tol, err.max()
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("b", [16, 32, 64])
+def test_sizes_inside_a_group(kernel, b):
+    # every third point of a grid is 1 in all vectors, the others 1e-7, 1e-13 and
+    # 1e-30; the correlation length is a fraction of the spacing, so that a row
+    # sees little but its own column
+    X = tensor_grid_points((24, 20, 17) if b == 16 else (19, 18, 12))
+    Y = np.abs(normal_block(31, len(X), b)) + 0.5
+    Y *= np.array([1.0, 1e-7, 1.0, 1e-13, 1.0, 1e-30])[np.arange(len(X)) % 6][:, None]
+    Y[:, 3] = np.abs(normal_block(32, len(X), 1))[:, 0] + 0.5
+    _check(kernel, 0.2 / 24 if kernel == K.KA_GAUSSIAN else 0.03 / 24, X, X, Y)
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("b", [16, 32, 64])
+@pytest.mark.parametrize("holes", [3, 40, 700])
+def test_single_gaps(kernel, b, holes):
+    # zeros and very small entries here and there: a row at one of them sees only
+    # its neighbours, at 2e-12 and less
+    X = tensor_grid_points((24, 20, 17) if b == 16 else (19, 18, 12))
+    Y = np.abs(normal_block(37, len(X), b)) + 0.5
+    at = np.random.default_rng(38).choice(len(X), holes, replace=False)
+    Y[at, at % b] = np.where(at % 3 == 0, 0.0, 1e-25)
+    _check(kernel, 0.2 / 24 if kernel == K.KA_GAUSSIAN else 0.037 / 24, X, X, Y)
+
+
+@pytest.mark.parametrize("precision", [K.KA_FP32, K.KA_BF16X3])
+def test_few_nonzero_rows(precision):
+    # columns of the kernel matrix: unit vectors, and some of them scaled
+    X = tensor_grid_points((20, 19, 18))
+    Y = np.zeros((len(X), 16))
+    Y[np.arange(16) * 397 + 5, np.arange(16)] = 10.0 ** np.arange(-8, 8)
+    _check(K.KA_GAUSSIAN, 0.2, X, X, Y, precision=precision)
+    if precision == K.KA_FP32:
+        _check(K.KA_EXP_L1, 0.05, X, X, Y)
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("b,nr,nc", [(16, 3000, 9000), (64, 1700, 4000)])
+def test_rows_without_near_columns(kernel, b, nr, nc):
+    # scattered columns with a hole, rows in it: every group's box is the cube
+    C = uniform_points(33, 2 * nc)
+    hole, centre = (0.17, 0.5) if kernel == K.KA_GAUSSIAN else (0.2, 0.5)
+    C = C[(np.abs(C - centre).sum(1) if kernel == K.KA_EXP_L1 else np.linalg.norm(C - centre, axis=1)) > hole][:nc]
+    X = np.concatenate([uniform_points(34, nr - 500), centre + 0.03 * (uniform_points(35, 500) - 0.5)])
+    assert len(C) == nc
+    ell, tol = (0.04, 2e-5) if kernel == K.KA_GAUSSIAN else (0.01, 2.2e-5)
+    _check(kernel, ell, X - 0.5, C - 0.5, normal_block(36, nc, b), tol)
