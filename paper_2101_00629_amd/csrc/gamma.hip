@@ -958,6 +958,14 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
   // 512-column splits against these): b = 16, 343 points 17.1 / 11.2, 1,000
   // points 38.8 / 11.1, 2,028 points 33.0 / 11.8, 3,366 points 29.8 / 18.4,
   // 4,913 points 31.9 / 25.3; b = 64, 1,000 points 46.4 / 13.6.
+  // With many rows and few columns the sums cost more than the shorter chains
+  // save.  A column takes a workgroup 0.030 us (b = 16), 0.047 or 0.038; partial
+  // sums, written and read, 1 us per 1.2 MB, and their launch 3 us.  Measured (us,
+  // unsplit / fine): b = 16, 10,000 x 600 27.7 / 21.7, 20,000 x 300 20.0 / 21.5,
+  // 33,000 x 600 28.0 / 26.7, 66,000 x 130 22.3 / 27.1, 130,000 x 130 23.2 / 37.4;
+  // b = 32, 10,000 x 300 31.2 / 25.2, 20,000 x 300 31.5 / 36.1, 130,000 x 65 28.1 /
+  // 65.3; b = 64, 10,000 x 600 32.2 / 27.1, 10,000 x 300 22.1 / 26.8, 33,000 x 65
+  // 17.6 / 35.0.
   p.fine_nsplit = 0;
   p.fine_cols = 0;
   p.fine_partial_bytes = 0;
@@ -966,7 +974,9 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
     const int64_t group = kFlushTiles * kCT;
     const int64_t fc = want <= kCT ? kCT : (want + group - 1) / group * group;
     const int64_t nf = (nc + fc - 1) / fc;
-    if (nf > p.nsplit) {
+    const double saved = (double)(std::min(cps, nc) - fc) * (b == 16 ? 0.030 : (b == 32 ? 0.047 : 0.038));
+    const double sums = ((double)(nf - p.nsplit) + (p.nsplit == 1 ? 1.0 : 0.0)) * nr * b * sizeof(float);
+    if (nf > p.nsplit && saved > sums / 1.2e6 + (p.nsplit == 1 ? 3.0 : 0.0)) {
       p.fine_nsplit = (int)nf;
       p.fine_cols = fc;
       p.fine_partial_bytes = (size_t)nf * nr * b * sizeof(float);

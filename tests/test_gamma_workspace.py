@@ -1,0 +1,23 @@
+"""Scratch that the kernel product states (no GPU): columns go in finer splits,
+with partial sums, only where these cost less than the shorter chains save."""
+import pytest
+
+import paper_2101_00629_amd as K
+
+
+@pytest.mark.parametrize("b", [16, 32, 64])
+@pytest.mark.parametrize("precision", [K.KA_FP32, K.KA_BF16X3])
+def test_many_rows_and_few_columns_take_no_partial_sums(b, precision):
+    sizes = [(20000, 65), (33000, 65), (33000, 130), (66000, 65), (66000, 130), (130000, 65), (500000, 65)]
+    for nr, nc in sizes:
+        if nr * nc * b >= 4e8:   # split FP16
+            continue
+        ysplit = -(-nc // 64) * 64 * b * 4 if precision == K.KA_BF16X3 else 0
+        assert K.ka_gamma_workspace(nr, nc, b, precision) == ysplit, (nr, nc)
+
+
+@pytest.mark.parametrize("b", [16, 32, 64])
+def test_small_products_keep_their_fine_splits(b):
+    for nr, nc in [(300, 1000), (1000, 1000), (3000, 600), (3000, 1000)]:
+        # more partial sums than splits of 512 columns have
+        assert K.ka_gamma_workspace(nr, nc, b, K.KA_FP32) > max(1, nc // 512) * nr * b * 4, (nr, nc)
