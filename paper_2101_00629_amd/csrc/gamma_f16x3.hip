@@ -462,7 +462,9 @@ __device__ __forceinline__ void exact_columns(const GammaLaunch& a, const double
       exact_point(a, wp[s], z);
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
-        const float e = on ? exact_value<KERNEL>(x[rb], z) : 0.f;
+        float e = exact_value<KERNEL>(x[rb], z);
+        asm("" : "+v"(e));   // (or each value gets a branch of its own)
+        e = on ? e : 0.f;
 #pragma unroll
         for (int t = 0; t < NT; ++t)
           acc[rb][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(e, on ? wy[s][t] : 0.f, acc[rb][t], 0, 0, 0);
@@ -1084,8 +1086,18 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
   __shared__ float s_inv[2][ROWS];
   __shared__ float s_lost[ROWS];
   __shared__ int s_best[ROWS];
-  __shared__ int s_flags, s_marks, s_size, s_cnt[4], s_few[kFewMarks];
-  if (threadIdx.x == 0) s_flags = s_marks = s_size = 0;   // (gram_rows has a barrier)
+  __shared__ int s_flags, s_marks, s_size, s_look, s_cnt[4], s_few[kFewMarks];
+  const int64_t row0 = rblk * ROWS;
+  const int64_t c0s = (int64_t)split * a.cols_per_split;
+  const int64_t c1s = c0s + a.cols_per_split < a.nc ? c0s + a.cols_per_split : a.nc;
+  const int64_t g0 = c0s / kGroup, g1 = (c1s + kGroup - 1) / kGroup;
+  // (the first loads of what follows the rows' box)
+  const int64_t own = row0 + threadIdx.x % ROWS;
+  const float* xr = a.xr + (own < a.nr ? own : a.nr - 1) * a.xr_stride;
+  const float x[3] = {xr[0], xr[1], xr[2]};
+  const int64_t g_own = g0 + threadIdx.x < g1 ? g0 + threadIdx.x : g0;
+  float flag_own = a.gbox[8 * g_own + 3], size_own = a.gbox[8 * g_own + 7];
+  if (threadIdx.x == 0) s_flags = s_marks = s_size = s_look = 0;   // (gram_rows has a barrier)
   double cl[3];
   launch_centre(a, cl);
   float c0, c1, c2;
@@ -1093,20 +1105,16 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
   c0 = uniform(row_centre<KERNEL>(s_box, 0, c0));
   c1 = uniform(row_centre<KERNEL>(s_box, 1, c1));
   c2 = uniform(row_centre<KERNEL>(s_box, 2, c2));
-  const int64_t row0 = rblk * ROWS;
-  const int64_t c0s = (int64_t)split * a.cols_per_split;
-  const int64_t c1s = c0s + a.cols_per_split < a.nc ? c0s + a.cols_per_split : a.nc;
-  const int64_t g0 = c0s / kGroup, g1 = (c1s + kGroup - 1) / kGroup;
-  // the flags of the columns' groups, their marked columns and the largest size of
-  // Y (the row's point is on its way meanwhile)
-  const int64_t own = row0 + threadIdx.x % ROWS;
-  const float* xr = a.xr + (own < a.nr ? own : a.nr - 1) * a.xr_stride;
-  const float x[3] = {xr[0], xr[1], xr[2]};
+  // the flags of the columns' groups, their marked columns and the largest size of Y
   int flags = 0, size = 0;
   for (int64_t g = g0 + threadIdx.x; g < g1; g += kThreads) {
-    const int f = (int)a.gbox[8 * g + 3];
+    if (g > g_own) {
+      flag_own = a.gbox[8 * g + 3];
+      size_own = a.gbox[8 * g + 7];
+    }
+    const int f = (int)flag_own;
     flags |= f & (kMarks - 1);
-    size = max(size, __builtin_bit_cast(int, a.gbox[8 * g + 7]));   // (not negative: in order as integers too)
+    size = max(size, __builtin_bit_cast(int, size_own));   // (not negative: in order as integers too)
     if (f > kMarks * kFewMarks) {
       atomicAdd(&s_marks, f / kMarks);
     } else if (f >= kMarks) {
@@ -1156,7 +1164,9 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
       for (int t = 0; t < B / 16; ++t) all = all && fabs(tot[rb][t][r]) < largest;
       low = low || all;
     }
-  const bool look = __syncthreads_or(low || (flags & kGaps)) != 0;
+  if (__any(low) && lane == 0) s_look = 1;
+  __syncthreads();
+  const bool look = s_look || (flags & kGaps);
   if (look) {
     if (threadIdx.x < ROWS) {
       float x[3];
