@@ -174,7 +174,7 @@ static size_t setup_bytes(const ka_desc* d, const Sizes& z) {
   s += block_bytes((size_t)z.n_rows * 4) + block_bytes((size_t)z.n_cols * 4);
   s += 2 * block_bytes((size_t)z.N * b * 8);
   s += 2 * block_bytes((size_t)transfer_points(d, z) * b * 4);
-  s += block_bytes(gamma_plan(z.n_rows, z.n_cols, b, d->precision).work_bytes);
+  s += block_bytes(gamma_plan(z.n_rows, z.n_cols, d->kernel, b, d->precision).work_bytes);
   if (d->domain == KA_NURBS && d->method == KA_COLLOCATION) s += block_bytes((size_t)z.n_rows * 8);   // W(g), FP64
   return s;
 }
@@ -427,7 +427,7 @@ static int setup_impl(const ka_desc* d, hipStream_t stream, Problem** out, const
   const int64_t big = transfer_points(d, z);
   P->w32a = (float*)dev_alloc(P, (size_t)big * b * 4, ok);
   P->w32b = (float*)dev_alloc(P, (size_t)big * b * 4, ok);
-  const GammaPlan gp = gamma_plan(P->n_rows, P->n_cols, b, d->precision);
+  const GammaPlan gp = gamma_plan(P->n_rows, P->n_cols, d->kernel, b, d->precision);
   P->gpart_bytes = gp.work_bytes;
   P->gpart = (float*)dev_alloc(P, gp.work_bytes, ok);
   if (!ok) {
@@ -599,7 +599,7 @@ GammaLaunch gamma_job(Problem* P) {
   g.coord_scale_lo = 0.0f;   // prescaled in FP64
   g.out_scale = P->out_scale;
   g.nv = P->b;
-  const GammaPlan gp = gamma_plan(g.nr, g.nc, P->b, P->d.precision);
+  const GammaPlan gp = gamma_plan(g.nr, g.nc, P->d.kernel, P->b, P->d.precision);
   g.nsplit = gp.nsplit;
   g.cols_per_split = gp.cols_per_split;
   g.row_blocks = gp.row_blocks;

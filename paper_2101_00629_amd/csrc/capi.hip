@@ -83,7 +83,7 @@ int ka_eigs(ka_problem* p, int M, double tol, int maxit, double* lambda_host, in
 
 size_t ka_gamma_workspace(int64_t nr, int64_t nc, int b, int precision) {
   if (nr <= 0 || nc <= 0) return 0;
-  return gamma_plan(nr, nc, b, precision).stated_bytes;
+  return gamma_stated_bytes(nr, nc, b, precision);
 }
 
 int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, int64_t nr, const float* xc_dev,
@@ -97,7 +97,7 @@ int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, in
   if (nr == 0) return KA_OK;
   if (!xr_dev || !Z_dev || (nc > 0 && (!xc_dev || !Y_dev))) return fail(KA_ERR_ARG, "NULL pointer");
   if (((uintptr_t)Y_dev & 15) != 0) return fail(KA_ERR_ARG, "Y must be 16-byte aligned");
-  const GammaPlan gp = gamma_plan(nr, nc, b, precision);
+  const GammaPlan gp = gamma_plan(nr, nc, kernel, b, precision);
   if (gp.base_bytes > work_bytes || (gp.base_bytes > 0 && !work_dev))
     return fail(KA_ERR_ARG, "workspace too small (see ka_gamma_workspace)");
   if (((uintptr_t)work_dev & 15) != 0) return fail(KA_ERR_ARG, "workspace must be 16-byte aligned");

@@ -881,10 +881,10 @@ static int rows_per_block(int b, int precision) {
 }
 
 constexpr int64_t kMinSplitCols = 512;
-constexpr double kF16MinWork = 4e8;
+constexpr double kF16MinWork = 4e8, kF16MinWorkExp16 = 1.3e9;
 constexpr int64_t kFineTarget = 512;
 
-GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
+GammaPlan gamma_plan(int64_t nr, int64_t nc, int kernel, int b, int precision) {
   GammaPlan p;
   p.rows_per_block = rows_per_block(b, precision);
   p.row_blocks = (nr + p.rows_per_block - 1) / p.rows_per_block;
@@ -895,8 +895,8 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
     p.partial_bytes = 0;
     p.ysplit_bytes = 0;
     p.base_bytes = 0;
+    p.fast_bytes = 0;
     p.work_bytes = 0;
-    p.stated_bytes = 0;
     p.f16 = false;
     p.fine_nsplit = 0;
     p.fine_cols = 0;
@@ -930,17 +930,25 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
   // its column range is fetched from HBM into that XCD's L2 once.
   if (ns >= kXcds) ns = (ns + kXcds - 1) / kXcds * kXcds;
   // The split-FP16 product (gamma_f16x3.hip) pays for its pre-pass from about
-  // kF16MinWork pairs times vectors on.  Measured on square products (us, FP32
-  // with the fine splits below / split FP16): b = 16, 4,913 points (3.9e8) 25.3 /
-  // 35.2 exponential, 27.4 / 30.8 Gaussian, 6,500 points (6.8e8) 32.7 / 40.7 and
-  // 34.0 / 34.7, 8,000 points (1.0e9) 40.4 / 41.4 and 40.4 / 35.3; b = 32, 3,375
-  // points (3.6e8) 23.4 / 38.4 exponential, 4,913 points (7.7e8) 38.4 / 39.6 and
-  // 49.0 / 35.4; b = 64, 2,028 points (2.6e8) 14.2 / 33.6 exponential, 3,375
-  // points (7.3e8) 29.8 / 33.2, 4,913 points (1.5e9) 56.2 / 44.7.  A product with
-  // b = 16 whose columns are not split has had no scratch, which its callers rely
-  // on, and keeps the FP32 matrix cores (524,288 rows and more, or under 1,024
-  // columns).
-  const bool f16 = (b != 16 || ns > 1) && (double)nr * nc * b >= kF16MinWork;
+  // kF16MinWork pairs times vectors on, the exponential kernel at b = 16 from
+  // kF16MinWorkExp16.  Measured (us, split FP16 / FP32 with the fine splits below):
+  // Gaussian, b = 16 5,832 points (5.4e8) 33.4 / 38.1, 6,500 37.1 / 34.7, 8,000
+  // (1.0e9) 38.0 / 40.8; b = 32 4,096 points (5.4e8) 30.3 / 38.7; b = 64 2,900
+  // points (5.4e8) 40.9 / 38.1, 3,375 34.1 / 34.9, 4,096 31.3 / 37.5.  Exponential,
+  // b = 16 6,500 points (6.8e8) 43.8 / 34.6, 8,000 (1.0e9) 43.9 / 41.3, 10,000 (1.6e9)
+  // 64.9 / 69.4, 20,000 x 1,300 (4.2e8) 39.7 / 27.3; b = 32 4,096 points 35.0 / 28.2,
+  // 4,913 (7.7e8) 42.0 / 38.2, 5,832 (1.1e9) 43.9 / 50.2, 12,167 x 3,000 43.4 / 47.2; b
+  // = 64 3,375 points 37.2 / 33.1, 4,096 (1.1e9) 33.8 / 35.3, 20,000 x 1,300 47.5 /
+  // 61.7.  (Below 1e9 the line for b = 32 and 64 could lie higher for the
+  // exponential kernel; there it is still ahead of the unsplit FP32 product.)  With
+  // one or two tiles of columns the exponential kernel does not earn it back
+  // either: 130,000 x 65, b = 64 37.4 / 28.5 us, 300,000 x 65, b = 32 47.5 / 36.9,
+  // 300,000 x 130 53.2 / 62.9.  A product with b = 16 whose columns are not split has
+  // had no scratch, which its callers rely on, and keeps the FP32 matrix cores
+  // (524,288 rows and more, or under 1,024 columns).
+  const bool exp32 = kernel == KA_EXP_L1 && precision == KA_FP32;
+  const bool f16 = (b != 16 || ns > 1) && !(kernel == KA_EXP_L1 && nc <= 2 * kCT) &&
+                   (double)nr * nc * b >= (exp32 && b == 16 ? kF16MinWorkExp16 : kF16MinWork);
   // Whole tile groups per split: only the last split can end in a padding tile.
   int64_t cps = (nc + ns - 1) / ns;
   cps = (cps + kFlushTiles * kCT - 1) / (kFlushTiles * kCT) * (kFlushTiles * kCT);
@@ -983,14 +991,19 @@ GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision) {
     }
   }
   const size_t part = (p.partial_bytes + 255) / 256 * 256;
-  const size_t fast = p.fine_nsplit > 0 ? (p.fine_partial_bytes + 255) / 256 * 256
-                                        : part + (f16 ? (gamma_f16x3_bytes(nc, b) + 255) / 256 * 256 : 0);
+  p.fast_bytes = p.fine_nsplit > 0 ? (p.fine_partial_bytes + 255) / 256 * 256
+                                         : part + (f16 ? (gamma_f16x3_bytes(nc, b) + 255) / 256 * 256 : 0);
   p.f16 = f16;
   p.base_bytes = part + p.ysplit_bytes;
-  p.work_bytes = f16 ? std::max(fast, p.base_bytes) : (p.fine_nsplit > 0 ? fast : part) + p.ysplit_bytes;
-  p.stated_bytes = fast + p.ysplit_bytes;
+  p.work_bytes = f16 ? std::max(p.fast_bytes, p.base_bytes) : (p.fine_nsplit > 0 ? p.fast_bytes : part) + p.ysplit_bytes;
   p.xcd_splits = ns_grid >= kXcds ? (int)ns_grid : 0;
   return p;
+}
+
+size_t gamma_stated_bytes(int64_t nr, int64_t nc, int b, int precision) {
+  size_t fast = 0;
+  for (int kernel : {KA_GAUSSIAN, KA_EXP_L1}) fast = std::max(fast, gamma_plan(nr, nc, kernel, b, KA_FP32).fast_bytes);
+  return fast + gamma_plan(nr, nc, KA_GAUSSIAN, b, precision).ysplit_bytes;
 }
 
 uint4* gamma_ysplit_ptr(float* work, const GammaPlan& p) {
@@ -1034,7 +1047,7 @@ static hipError_t launch_kernel_variant(const GammaLaunch& a, int b, int precisi
 
 hipError_t launch_gamma(GammaLaunch a, size_t work_bytes, int kernel, int b, int precision, hipStream_t s) {
   if (a.nr <= 0) return hipSuccess;
-  GammaPlan p = gamma_plan(a.nr, a.nc, b, precision);
+  GammaPlan p = gamma_plan(a.nr, a.nc, kernel, b, precision);
   if (p.fine_nsplit > 0 && work_bytes >= p.work_bytes) {
     p.nsplit = p.fine_nsplit;
     p.cols_per_split = p.fine_cols;

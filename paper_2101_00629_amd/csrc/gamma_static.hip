@@ -54,7 +54,7 @@ int ka_gamma_apply_static(int kernel, double sigma, double ell, const float* xr_
   if (nr == 0) return KA_OK;
   if (!xr_dev || !Z_dev || (nc > 0 && (!xc_dev || !Y_dev))) return fail(KA_ERR_ARG, "NULL pointer");
   if (((uintptr_t)Y_dev & 15) != 0) return fail(KA_ERR_ARG, "Y must be 16-byte aligned");
-  const GammaPlan gp = gamma_plan(nr, nc, b, precision);
+  const GammaPlan gp = gamma_plan(nr, nc, kernel, b, precision);
   if (gp.base_bytes > kStaticScratchBytes)
     return fail(KA_ERR_ARG, "product needs " + std::to_string(gp.base_bytes) + " scratch bytes, more than the " +
                                 std::to_string(kStaticScratchBytes) + " of the static scratch (use ka_gamma_apply)");

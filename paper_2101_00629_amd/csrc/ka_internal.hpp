@@ -49,7 +49,7 @@ struct GammaPlan {
   size_t ysplit_bytes;    // BF16X3: pre-split Y, ceil(nc / 64) * 64 * b * 4 bytes; 0 for FP32
   size_t base_bytes;      // least scratch: partials (256-byte aligned), then the pre-split Y
   size_t work_bytes;      // scratch of the fastest path at this precision (base_bytes or more)
-  size_t stated_bytes;    // ka_gamma_workspace: enough for it at either precision
+  size_t fast_bytes;      // its partials and FP16 operands
   bool f16;               // contraction on the FP16 matrix cores where the scratch holds work_bytes
   int xcd_splits;         // 0, or the split count rounded up to the XCD count (grouped grid)
   int fine_nsplit;        // 0, or the splits to take where the scratch holds work_bytes
@@ -57,7 +57,9 @@ struct GammaPlan {
   size_t fine_partial_bytes;
 };
 
-GammaPlan gamma_plan(int64_t nr, int64_t nc, int b, int precision);
+GammaPlan gamma_plan(int64_t nr, int64_t nc, int kernel, int b, int precision);
+// ka_gamma_workspace: enough for the fastest path of either kernel
+size_t gamma_stated_bytes(int64_t nr, int64_t nc, int b, int precision);
 // Start of the pre-split Y inside a product's scratch `work` (BF16X3), or nullptr.
 uint4* gamma_ysplit_ptr(float* work, const GammaPlan& p);
 

@@ -21,3 +21,10 @@ def test_small_products_keep_their_fine_splits(b):
     for nr, nc in [(300, 1000), (1000, 1000), (3000, 600), (3000, 1000)]:
         # more partial sums than splits of 512 columns have
         assert K.ka_gamma_workspace(nr, nc, b, K.KA_FP32) > max(1, nc // 512) * nr * b * 4, (nr, nc)
+
+
+def test_exponential_products_that_split_fp16_does_not_pay_for():
+    # the scratch is for either kernel, that of the routes in FP32 included
+    for nr, nc, b in [(20000, 1300, 16), (5832, 5832, 16), (130000, 65, 64), (300000, 65, 32)]:
+        f16 = -(-nc // 512) * 512 * (4 * b + 64)
+        assert K.ka_gamma_workspace(nr, nc, b, K.KA_FP32) >= f16, (nr, nc, b)

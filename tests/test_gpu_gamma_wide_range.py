@@ -28,7 +28,9 @@ def _check(kernel, ell, X, C, Y, tol=1e-5, precision=K.KA_FP32):
     xr, xc, y = torch.tensor(X, **d), torch.tensor(C, **d), torch.tensor(Y, **d)
     z = torch.full((len(X), Y.shape[1]), float("nan"), **d)
     nb = K.ka_gamma_workspace(len(X), len(C), Y.shape[1], precision)
-    assert len(X) * len(C) * Y.shape[1] > 4e8 and nb >= len(C) * (4 * Y.shape[1] + 64)   # the split-FP16 route
+    # the split-FP16 route
+    least = 1.3e9 if kernel == K.KA_EXP_L1 and Y.shape[1] == 16 else 4e8
+    assert len(X) * len(C) * Y.shape[1] > least and nb >= len(C) * (4 * Y.shape[1] + 64)
     work = torch.full((nb // 4,), float("nan"), **d)
     K.ka_gamma_apply(kernel, 1.0, ell, xr, xc, y, z, precision, work)
     Z = z.cpu().numpy().astype(np.float64)
@@ -48,7 +50,7 @@ def test_sizes_inside_a_group(kernel, b):
     # every third point of a grid is 1 in all vectors, the others 1e-7, 1e-13 and
     # 1e-30; the correlation length is a fraction of the spacing, so that a row
     # sees little but its own column
-    X = tensor_grid_points((24, 20, 17) if b == 16 else (19, 18, 12))
+    X = tensor_grid_points((24, 22, 18) if b == 16 else (19, 18, 12))
     Y = np.abs(normal_block(31, len(X), b)) + 0.5
     Y *= np.array([1.0, 1e-7, 1.0, 1e-13, 1.0, 1e-30])[np.arange(len(X)) % 6][:, None]
     Y[:, 3] = np.abs(normal_block(32, len(X), 1))[:, 0] + 0.5
@@ -61,7 +63,7 @@ def test_sizes_inside_a_group(kernel, b):
 def test_single_gaps(kernel, b, holes):
     # zeros and very small entries here and there: a row at one of them sees only
     # its neighbours, at 2e-12 and less
-    X = tensor_grid_points((24, 20, 17) if b == 16 else (19, 18, 12))
+    X = tensor_grid_points((24, 22, 18) if b == 16 else (19, 18, 12))
     Y = np.abs(normal_block(37, len(X), b)) + 0.5
     at = np.random.default_rng(38).choice(len(X), holes, replace=False)
     Y[at, at % b] = np.where(at % 3 == 0, 0.0, 1e-25)
@@ -71,7 +73,7 @@ def test_single_gaps(kernel, b, holes):
 @pytest.mark.parametrize("precision", [K.KA_FP32, K.KA_BF16X3])
 def test_few_nonzero_rows(precision):
     # columns of the kernel matrix: unit vectors, and some of them scaled
-    X = tensor_grid_points((20, 19, 18))
+    X = tensor_grid_points((22, 21, 20))
     Y = np.zeros((len(X), 16))
     Y[np.arange(16) * 397 + 5, np.arange(16)] = 10.0 ** np.arange(-8, 8)
     _check(K.KA_GAUSSIAN, 0.2, X, X, Y, precision=precision)
@@ -80,7 +82,7 @@ def test_few_nonzero_rows(precision):
 
 
 @pytest.mark.parametrize("kernel", KERNELS)
-@pytest.mark.parametrize("b,nr,nc", [(16, 3000, 9000), (64, 1700, 4000)])
+@pytest.mark.parametrize("b,nr,nc", [(16, 9000, 9100), (64, 1700, 4000)])
 def test_rows_without_near_columns(kernel, b, nr, nc):
     # scattered columns with a hole, rows in it: every group's box is the cube
     C = uniform_points(33, 2 * nc)
