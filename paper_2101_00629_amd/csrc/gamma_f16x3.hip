@@ -433,9 +433,10 @@ __device__ __forceinline__ void exact_point(const GammaLaunch& a, const float* p
 // The n columns column(0), column(1), ... against RB groups of 16 rows, added to
 // `tot`; sixteen at a time, the operands of the next sixteen or 32 on their way.
 template <int KERNEL, int B, int RB, class Column>
-__device__ __forceinline__ void exact_columns(const GammaLaunch& a, const double (&x)[RB][3], int n, Column column,
-                                              d4v (&tot)[RB][B / 16]) {
+__device__ __forceinline__ void exact_columns(const GammaLaunch& a, const double (&x)[RB][3], int columns,
+                                              Column column, d4v (&tot)[RB][B / 16]) {
   constexpr int NT = B / 16;
+  const int n = __builtin_amdgcn_readfirstlane(columns);
   const int q = (threadIdx.x & 63) >> 4, l16 = threadIdx.x & 15;
   float p[2][4][3], y[2][4][NT];
   auto load = [&](int i0, float (&lp)[4][3], float (&ly)[4][NT]) {
@@ -457,6 +458,7 @@ __device__ __forceinline__ void exact_columns(const GammaLaunch& a, const double
   auto work = [&](int i0, const float (&wp)[4][3], const float (&wy)[4][NT]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
+      if (i0 + 4 * s >= n) break;   // (a mark or two as a rule)
       const bool on = i0 + 4 * s + q < n;
       double z[3];
       exact_point(a, wp[s], z);
@@ -473,13 +475,13 @@ __device__ __forceinline__ void exact_columns(const GammaLaunch& a, const double
   };
   if (n <= 0) return;
   load(0, p[0], y[0]);
-  load(16, p[1], y[1]);
+  if (n > 16) load(16, p[1], y[1]);
   for (int i0 = 0; i0 < n; i0 += 32) {
     work(i0, p[0], y[0]);
-    load(i0 + 32, p[0], y[0]);
+    if (i0 + 32 < n) load(i0 + 32, p[0], y[0]);
     __builtin_amdgcn_sched_barrier(0);
     work(i0 + 16, p[1], y[1]);
-    load(i0 + 48, p[1], y[1]);
+    if (i0 + 48 < n) load(i0 + 48, p[1], y[1]);
     __builtin_amdgcn_sched_barrier(0);
     if ((i0 & 127) == 96 || i0 + 32 >= n)
 #pragma unroll
@@ -1118,8 +1120,12 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
     if (f > kMarks * kFewMarks) {
       atomicAdd(&s_marks, f / kMarks);
     } else if (f >= kMarks) {
+      uint4 m[kGroup / 128];   // (all at once: word by word they are 16 waits)
+#pragma unroll
+      for (int k = 0; k < kGroup / 128; ++k) m[k] = reinterpret_cast<const uint4*>(a.gmask + g * (kGroup / 32))[k];
+#pragma unroll
       for (int k = 0; k < kGroup / 32; ++k)
-        for (uint32_t w = a.gmask[g * (kGroup / 32) + k]; w; w &= w - 1) {
+        for (uint32_t w = k % 4 == 0 ? m[k / 4].x : (k % 4 == 1 ? m[k / 4].y : (k % 4 == 2 ? m[k / 4].z : m[k / 4].w)); w; w &= w - 1) {
           const int64_t c = g * kGroup + 32 * k + __builtin_ctz(w);
           if (c < c0s || c >= c1s) continue;
           const int at = atomicAdd(&s_marks, 1);
