@@ -161,7 +161,7 @@ void kl_field_kernel(const double* __restrict__ Phi, int64_t ldp, int64_t P, con
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
-      for (int t = 0; t < kT; ++t) acc[u][t] = (d4v){mu, mu, mu, mu};
+      for (int t = 0; t < kT; ++t) acc[u][t] = (d4v){0.0, 0.0, 0.0, 0.0};
     // each step's operands are replaced as soon as its MFMAs are issued; the
     // scheduling barriers keep the compiler from sinking the loads
     int c = 0;
@@ -190,7 +190,7 @@ void kl_field_kernel(const double* __restrict__ Phi, int64_t ldp, int64_t P, con
 #pragma unroll
         for (int t = 0; t < kT; ++t)
           if (s0 + 16 * u + 4 * r < S && p0 + 16 * t + li < P)
-            __builtin_nontemporal_store(acc[u][t][r], row + 16 * t);
+            __builtin_nontemporal_store(mu + acc[u][t][r], row + 16 * t);   // (one rounding at mu's size, not one per step)
         row += 4 * ldf;
       }
   }
