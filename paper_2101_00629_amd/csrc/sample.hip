@@ -367,7 +367,6 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
   }
   // this call's workspace; the host's data (transposed grid matrices,
   // eigenvalues, the cleared flag) go up in one copy
-  const int chunk = std::min(M, 128);
   const int64_t tq = std::max((int64_t)mq[0] * n[1] * n[2], (int64_t)mq[0] * mq[1] * n[2]);
   const int64_t tg = std::max((int64_t)mg[0] * n[1] * n[2], (int64_t)mg[0] * mg[1] * n[2]);
   const int64_t clen = std::max<int64_t>(8192, (Q + 255) / 256);
@@ -385,24 +384,40 @@ extern "C" int ka_kl_sample(ka_problem* p, int M, const double* lambda_host, con
   up.insert(up.end(), lambda_host, lambda_host + M);
   const size_t obad = up.size();
   up.push_back(0.0);
+  // Vectors that go through the mode products together: up to 128 (a block of 16
+  // to 64 leaves small grids latency-bound), but no more than 1 GiB of
+  // intermediate blocks takes, or 32: on a grid that is fine in two directions
+  // only these are larger than everything else.
+  const double per_vector = (2.0 * (double)std::max(tq, tg) + (double)Q) * sizeof(double);
+  int chunk = std::min(M, (int)std::max(32.0, std::min(128.0, (double)(1 << 30) / per_vector)));
   KlArena ar;
-  const size_t iup = ar.add(up.size());
-  const size_t it1 = ar.add((size_t)std::max(tq, tg) * chunk), it2 = ar.add((size_t)std::max(tq, tg) * chunk);
-  const size_t iUq = ar.add((size_t)Q * chunk), ipart = ar.add((size_t)nchunk * chunk), inorm = ar.add(M);
-  const size_t iPhi = ar.add((size_t)Pts * M), igs = ar.add(gscale.size());
-  const size_t iXi = ar.add((size_t)Kp * Sp);
-  if (P->kl_bytes < ar.total) {
+  size_t iup, it1, it2, iUq, ipart, inorm, iPhi, igs, iXi;
+  for (;;) {
+    ar = KlArena();
+    iup = ar.add(up.size());
+    it1 = ar.add((size_t)std::max(tq, tg) * chunk);
+    it2 = ar.add((size_t)std::max(tq, tg) * chunk);
+    iUq = ar.add((size_t)Q * chunk);
+    ipart = ar.add((size_t)nchunk * chunk);
+    inorm = ar.add(M);
+    iPhi = ar.add((size_t)Pts * M);
+    igs = ar.add(gscale.size());
+    iXi = ar.add((size_t)Kp * Sp);
+    if (P->kl_bytes >= ar.total) break;
     if (P->kl_buf) {
       (void)hipStreamSynchronize(s);
       (void)hipFree(P->kl_buf);
       P->kl_buf = nullptr;
       P->kl_bytes = 0;
     }
-    if (hipMalloc(&P->kl_buf, ar.total) != hipSuccess) {
-      P->kl_buf = nullptr;
-      return fail(KA_ERR_OOM, "device allocation failed in ka_kl_sample");
+    if (hipMalloc(&P->kl_buf, ar.total) == hipSuccess) {
+      P->kl_bytes = ar.total;
+      break;
     }
-    P->kl_bytes = ar.total;
+    (void)hipGetLastError();
+    P->kl_buf = nullptr;
+    if (chunk <= 32) return fail(KA_ERR_OOM, "device allocation failed in ka_kl_sample");
+    chunk = 32;
   }
   auto at = [&](size_t i) { return (double*)((char*)P->kl_buf + ar.off[i]); };
   double* up_d = at(iup);
