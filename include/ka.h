@@ -341,7 +341,9 @@ typedef struct ka_result {
  * fails); max_slots: requests solved at once (1..256). */
 int ka_server_create(size_t hbm_budget, int max_slots, ka_server** out);
 /* Device bytes a request holds while admitted: ka_footprint plus the
- * eigensolver workspace for M eigenpairs at the descriptor's block size. */
+ * eigensolver workspace for M eigenpairs at the descriptor's block size; a request
+ * whose kernel products run in shared launches does without the scratch that they
+ * would take on their own. */
 int ka_request_bytes(const ka_desc* desc, int M, size_t* bytes);
 /* lambda_host: caller-owned, lambda_len doubles, at least M (Galerkin) or 2M
  * (collocation, re/im interleaved), written when the request completes

@@ -162,7 +162,13 @@ static int64_t transfer_points(const ka_desc* d, const Sizes& z) {
   return big;
 }
 
-static size_t setup_bytes(const ka_desc* d, const Sizes& z) {
+// scratch of the kernel product
+static size_t product_bytes(const ka_desc* d, const Sizes& z, bool served) {
+  const GammaPlan gp = gamma_plan(z.n_rows, z.n_cols, d->kernel, d->block, d->precision);
+  return served && gp.row_blocks * gp.nsplit < kDirectItems ? gp.base_bytes : gp.work_bytes;
+}
+
+static size_t setup_bytes(const ka_desc* d, const Sizes& z, bool served) {
   const int b = d->block;
   size_t s = 0;
   for (int k = 0; k < 3; ++k) {
@@ -174,7 +180,7 @@ static size_t setup_bytes(const ka_desc* d, const Sizes& z) {
   s += block_bytes((size_t)z.n_rows * 4) + block_bytes((size_t)z.n_cols * 4);
   s += 2 * block_bytes((size_t)z.N * b * 8);
   s += 2 * block_bytes((size_t)transfer_points(d, z) * b * 4);
-  s += block_bytes(gamma_plan(z.n_rows, z.n_cols, d->kernel, b, d->precision).work_bytes);
+  s += block_bytes(product_bytes(d, z, served));
   if (d->domain == KA_NURBS && d->method == KA_COLLOCATION) s += block_bytes((size_t)z.n_rows * 8);   // W(g), FP64
   return s;
 }
@@ -427,9 +433,8 @@ static int setup_impl(const ka_desc* d, hipStream_t stream, Problem** out, const
   const int64_t big = transfer_points(d, z);
   P->w32a = (float*)dev_alloc(P, (size_t)big * b * 4, ok);
   P->w32b = (float*)dev_alloc(P, (size_t)big * b * 4, ok);
-  const GammaPlan gp = gamma_plan(P->n_rows, P->n_cols, d->kernel, b, d->precision);
-  P->gpart_bytes = gp.work_bytes;
-  P->gpart = (float*)dev_alloc(P, gp.work_bytes, ok);
+  P->gpart_bytes = product_bytes(d, z, region != nullptr);
+  P->gpart = (float*)dev_alloc(P, P->gpart_bytes, ok);
   if (!ok) {
     free_problem(P);
     return fail(KA_ERR_OOM, "device allocation failed in ka_setup");
@@ -644,11 +649,11 @@ int setup_problem(const ka_desc* d, hipStream_t stream, Problem** out, const Reg
   return setup_impl(d, stream, out, region);
 }
 
-int footprint(const ka_desc* d, size_t* bytes) {
+int footprint(const ka_desc* d, bool served, size_t* bytes) {
   Sizes z;
   int rc = check_desc(d, z);
   if (rc) return rc;
-  *bytes = setup_bytes(d, z);
+  *bytes = setup_bytes(d, z, served);
   return KA_OK;
 }
 

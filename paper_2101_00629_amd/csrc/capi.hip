@@ -36,7 +36,7 @@ int ka_desc_size(const ka_desc* desc, int64_t* N, int64_t* Ntilde, int64_t* Nqua
 
 int ka_footprint(const ka_desc* desc, size_t* device_bytes) {
   if (!device_bytes) return fail(KA_ERR_ARG, "device_bytes is NULL");
-  return footprint(desc, device_bytes);
+  return footprint(desc, false, device_bytes);
 }
 
 int ka_apply_A(ka_problem* p, int form, const double* X_dev, int64_t ldx, double* Y_dev, int64_t ldy, int nvec,

@@ -58,6 +58,10 @@ struct GammaPlan {
 };
 
 GammaPlan gamma_plan(int64_t nr, int64_t nc, int kernel, int b, int precision);
+// Work items (row blocks times splits of the base plan) at which a served
+// request's product fills the chip on its own; smaller ones run in batched
+// launches, in the base splits, and need the base scratch only.
+constexpr int64_t kDirectItems = 2048;
 // ka_gamma_workspace: enough for the fastest path of either kernel
 size_t gamma_stated_bytes(int64_t nr, int64_t nc, int b, int precision);
 // Start of the pre-split Y inside a product's scratch `work` (BF16X3), or nullptr.
@@ -260,7 +264,8 @@ int gamma_step(Problem* P, const float* Y, float* Z, int nv, hipStream_t s);
 void* problem_alloc(Problem* P, size_t bytes);
 // region: optional range every allocation of the problem comes from.
 int setup_problem(const ka_desc* d, hipStream_t stream, Problem** out, const Region* region = nullptr);
-int footprint(const ka_desc* d, size_t* bytes);
+// served: of a request, whose kernel product may be batched
+int footprint(const ka_desc* d, bool served, size_t* bytes);
 // N, Ntilde, Nquad that setup_problem would produce (host only).
 int desc_sizes(const ka_desc* d, int64_t* N, int64_t* Nt, int64_t* Nq);
 void destroy_problem(Problem* P);

@@ -53,8 +53,6 @@ namespace {
 
 using Clock = std::chrono::steady_clock;
 
-// work items at which a single product fills the chip without batching
-constexpr int64_t kDirectItems = 2048;
 // longest wait for other solves to reach their kernel product
 constexpr double kGatherSeconds = 150e-6;
 constexpr int kRing = 8;   // device job/item buffers in flight
@@ -419,7 +417,7 @@ extern "C" {
 int ka_request_bytes(const ka_desc* desc, int M, size_t* bytes) {
   if (!desc || !bytes) return fail(KA_ERR_ARG, "NULL argument");
   size_t fp = 0;
-  if (int rc = footprint(desc, &fp)) return rc;
+  if (int rc = footprint(desc, true, &fp)) return rc;
   int64_t N = 0;
   if (int rc = desc_sizes(desc, &N, nullptr, nullptr)) return rc;
   if (M < 1 || M > N) return fail(KA_ERR_ARG, "M must be in 1..N");
