@@ -909,6 +909,7 @@ __device__ __forceinline__ double block_sum(double s, double* s_sum) {
 // (N(0, 1) blocks of 287,496 x 64: a dozen entries in 50 row blocks get as far
 // as the check of the group, none further.)
 constexpr float kLostCut = 0x1p-19f;
+constexpr float kFarExponent = 86.f;   // from here on 2^-40 of a kernel value is below FP32's least, 2^-126
 constexpr int kEntries = 64;
 
 struct Lossy {
@@ -1189,7 +1190,7 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
           const float gap = fmaxf(fmaxf(b[k] - x[k], x[k] - b[4 + k]), 0.f);
           d += KERNEL == KA_GAUSSIAN ? gap * gap : gap;
         }
-        const float v = __builtin_amdgcn_exp2f(-d) * b[7];
+        const float v = d < kFarExponent ? __builtin_amdgcn_exp2f(-d) * b[7] : 0.f;
         lost += v;
         if (v > most) {
           most = v;
