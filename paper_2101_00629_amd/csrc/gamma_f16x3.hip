@@ -248,7 +248,7 @@ __device__ __forceinline__ void split16_group(const GammaLaunch& a, int kernel, 
   // of the odd ones.
   const float low = m > 0.f ? __builtin_ldexpf(1.f, ex - 22) : 0.f;
   uint32_t bad = 0, nz = ~0u;
-  if (__any(least < __builtin_bit_cast(uint32_t, low) || least == 0 || most >= 0x7f800000u)) {
+  if (__any(j < a.nv && (least < __builtin_bit_cast(uint32_t, low) || least == 0 || most >= 0x7f800000u))) {
     nz = 0;
     bool gap = m == 0.f;
 #pragma unroll
@@ -1171,7 +1171,7 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
       for (int t = 0; t < B / 16; ++t) all = all && fabs(tot[rb][t][r]) < largest;
       low = low || all;
     }
-  if (__any(low) && lane == 0) s_look = 1;
+  if (__any(low && (lane & 15) < a.nv) && lane == 0) s_look = 1;
   __syncthreads();
   const bool look = s_look || (flags & kGaps);
   if (look) {
@@ -1216,7 +1216,7 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
 #pragma unroll
         for (int t = 0; t < B / 16; ++t) {
           const bool low = fabs(tot[rb][t][r]) < lost;
-          some = some || low;
+          some = some || (low && 16 * t + (lane & 15) < a.nv);   // (vectors that do not count are zero)
           all = all && low;
           out[row * B + 16 * t + (lane & 15)] = (float)(f * tot[rb][t][r]);
         }
