@@ -55,12 +55,18 @@ enum ka_method { KA_GALERKIN_IBQ = 0,   /* Galerkin with interpolation-based qua
 enum ka_domain { KA_BOX = 0, KA_QUARTER_ANNULUS = 1, KA_NURBS = 2 /* general single-patch NURBS volume */ };
 enum ka_kernel { KA_GAUSSIAN = 0, /* sigma^2 exp(-|x-y|_2^2 / ell^2) */
                  KA_EXP_L1 = 1    /* sigma^2 exp(-|x-y|_1 / ell)     */ };
-enum ka_precision { KA_FP32 = 0,  /* FP32 kernel tiles, FP32 MFMA contraction; large
-                                     products contract pairs of FP16 parts that hold
-                                     FP32's significand (3 FP16 MFMAs, FP32 accumulation) */
-                    KA_BF16X3 = 1 /* FP32 tiles split hi+lo into BF16, 3 BF16 MFMAs,
-                                     FP32 accumulation; large Gaussian products as
-                                     KA_FP32, which is faster there                  */ };
+/* Precision of the kernel product.  Every entry of Z is within 1e-5 (KA_FP32) or 6e-5
+ * (KA_BF16X3) of |Gamma| |Y|, besides what rounding the points to FP32 does to Gamma.
+ * KA_FP32    kernel values in FP32, FP32 MFMA contraction.  Large products contract
+ *            pairs of FP16 parts: 22 bits and a sign of each value of Gamma and Y (FP32
+ *            has 24), 3 FP16 MFMAs, FP32 accumulation of 16 of them, FP64 totals.  The
+ *            rounding is smaller than that of FP32 MFMAs all the same; what the range
+ *            of FP16 does not hold (values not finite or far below the others of their
+ *            512 columns) is formed in FP32.
+ * KA_BF16X3  kernel values in FP32, split hi + lo into BF16, 3 BF16 MFMAs, FP32
+ *            accumulation; large Gaussian products as KA_FP32, which is faster there
+ *            and closer. */
+enum ka_precision { KA_FP32 = 0, KA_BF16X3 = 1 };
 enum ka_form { KA_A = 0,          /* the covariance matrix A itself                  */
                KA_APRIME = 1      /* the standard-form operator A' (Sec. 3, eq. standard):
                                      Galerkin L^-1 A L^-T, collocation Z^-1 A         */ };
@@ -249,26 +255,31 @@ int ka_eigs(ka_problem* p, int M, double tol, int maxit, double* lambda_host, in
  * 16-byte aligned): the split-K partial sums (nsplit * nr * b * 4 bytes when
  * the columns are split) and, for KA_BF16X3, Y split into hi/lo BF16 parts
  * (ceil(nc / 64) * 64 * b * 4 bytes).  Large KA_FP32 products (and Gaussian
- * KA_BF16X3 ones) split Y and the points into FP16 parts (about (4 b + 64) nc
- * bytes) and then run 1.5 to 3 times as fast; small products split their columns
- * further, with more partial sums.  With less scratch than that they run on the
- * FP32 (or BF16) matrix cores in coarser splits.
+ * KA_BF16X3 ones) split Y and the points into FP16 parts (about (4 b + 65) bytes
+ * per column, whole groups of 512 columns) and then run 1.1 (the smallest of these) to
+ * 3 times as fast; small products split their columns further, with more partial
+ * sums.  With less scratch than that they run on the FP32 (or BF16) matrix cores in
+ * coarser splits, with other roundings inside the same bounds; with less than the
+ * partial sums of these, KA_ERR_ARG.
  * Pass ka_gamma_workspace() bytes.  Async on `stream`. */
 int ka_gamma_apply(int kernel, double sigma, double ell, const float* xr_dev, int64_t nr,
                    const float* xc_dev, int64_t nc, const float* Y_dev, int b, float* Z_dev,
                    int precision, void* work_dev, size_t work_bytes, void* stream);
 
-/* Scratch bytes ka_gamma_apply needs for these sizes. */
+/* Scratch bytes with which ka_gamma_apply takes its fastest route at these sizes (the
+ * larger need of the two kernels). */
 size_t ka_gamma_workspace(int64_t nr, int64_t nc, int b, int precision);
 
 /* ka_gamma_apply without any device allocation and without a workspace
  * argument, for callers that cannot allocate device memory (code under HIP
  * stream capture, serving loops and harnesses that forbid hipMalloc).  Same
- * arguments, kernels and results as ka_gamma_apply; its scratch is a
- * file-scope device array of ka_gamma_static_capacity() bytes (128 MiB), one
+ * arguments and kernels as ka_gamma_apply, and the results that it has with as much
+ * scratch: a file-scope device array of ka_gamma_static_capacity() bytes (128 MiB), one
  * per GPU, held until the process ends and looked up on the first call on each
- * device.  A product whose ka_gamma_workspace() exceeds that capacity fails
- * with KA_ERR_ARG before anything is launched.  All calls on one GPU share the
+ * device.  A product whose ka_gamma_workspace() exceeds that capacity takes the
+ * route of less scratch (slower, with other roundings than with the full workspace);
+ * one whose coarsest partial sums exceed it fails with KA_ERR_ARG before anything is
+ * launched.  All calls on one GPU share the
  * array: calls that overlap on the device (concurrent streams) race and must
  * be serialised by the caller.  Nothing in the array needs clearing: every
  * entry a call reads is written earlier in the same call.  Async on `stream`. */
@@ -293,8 +304,9 @@ size_t ka_gamma_static_capacity(void);
  *   column-major FP64 (ldxi >= M), the draws (N(0,1) for a Gaussian field).
  * field_dev: P x nsamples column-major FP64 (ldf >= P), P = npts[0] npts[1]
  *   npts[2], grid point index i1 + npts[0] (i2 + npts[1] i3).
- * Its device workspace (about (P + quadrature points) x M doubles) is kept
- * by the problem between calls, grown when a call needs more, and freed by
+ * Its device workspace (about P x M doubles for the functions, M x nsamples for the
+ * draws, and three intermediate blocks of the grid or quadrature points times 32 vectors,
+ * or up to 128 where they take less than 1 GiB) is kept by the problem between calls, grown when a call needs more, and freed by
  * ka_destroy; collocation also keeps the quadrature data of the norms from
  * its first call.  Synchronizes `stream` before it returns.  Errors: KA_ERR_ARG (bad
  * sizes or values), KA_ERR_SINGULAR (an eigenfunction of zero norm),

@@ -420,9 +420,10 @@ hipError_t chol_upper_inv(const double* G, int n, int ldg, double* Rinv, int ldr
 // most the Rayleigh-Ritz order): diagonal-pivoted Cholesky with a rank cut and
 // the inverse of its factor (basis_core.hpp), one workgroup, working copy in
 // LDS up to order kBasisLds.  Its chain of 2 n steps takes 107 us on average over
-// the restarts of 50 collocation eigenpairs (n about 50 to 130); 206 us with a
-// division per entry of the trailing block, a maximum over the whole workgroup
-// and a sum over the row per entry of the inverse.  W (n x rank, leading dimension ldw) = P R^-1;
+// the restarts of a solve for 30 collocation eigenpairs (16 x 14 x 12 elements, p
+// = 2, exponential, b = 16); 205 us with a division per entry of the trailing
+// block, a maximum over the whole workgroup and a sum over the row per entry of
+// the inverse.  W (n x rank, leading dimension ldw) = P R^-1;
 // rank goes to a device int.
 // ---------------------------------------------------------------------------
 constexpr int kBasisThreads = 1024;

@@ -1,7 +1,8 @@
 // Fused covariance-kernel product Z = out_scale * diag(rs) * Gamma * Y with
 // Gamma[r][c] = exp2(-s(xr_r - xc_c)) evaluated on the fly and never stored.
 // This file has the planner, the FP32-matrix-core and split-BF16 products and
-// the batched launch; large FP32 products go to gamma_f16x3.hip.
+// the batched launch; large FP32 products, and Gaussian ones at split BF16, go to
+// gamma_f16x3.hip.
 //
 // This is the quadratic-cost step of both matrix-free operators: the Gamma
 // product of the Galerkin nine-step algorithm (paper Sec. 3.1) and step 3 of

@@ -25,8 +25,12 @@
 //   with no more than 64 that are not zero, are marked by the pre-pass, left out
 //   of the FP16 operands and added as they stand; where half of an item's
 //   columns are marked, all of it is formed so;
-// - rows whose results are too small for what the groups' boxes promise, which
-//   may be what was lost (lossy_results), are done again.
+// - rows (in vectors with zeros or very small entries, single entries) whose
+//   results are below 2^-19 of what the groups' boxes promise, which may be what
+//   was lost (lossy_results), are done again; where that is a quarter of an item's
+//   rows, all of it.
+// So what is lost is below 2^-19 of a result, or below 2^-126 |Y| (groups at
+// exponents past 86, where the loss is below FP32's least value).
 //
 // Exponents (Gaussian).  16 x 16 exponents -|x - y|^2 come from one
 // v_mfma_f32_16x16x32_f16.  Coordinates (scaled, relative to the launch's
@@ -47,10 +51,10 @@
 // that meet a point outside it take differences on the VALU, as the
 // exponential kernel does.
 //
-// What bounds it (287,496^2, b = 64, Gaussian, 32.5 ms = 2.54e12 pairs/s against
-// 91 ms on the FP32 matrix cores): matrix cores 54% and VALU 65% of the cycles,
-// 23% of them together, so that either is busy 97% of the time, at 2.0 GHz (the
-// power limit; 2.4 GHz nominal).  The same instructions without any memory
+// What bounds it (287,496^2, b = 64, Gaussian, 32.2 to 33.4 ms on several cards =
+// 2.5e12 pairs/s, against 91 ms on the FP32 matrix cores): matrix cores 53% and
+// VALU 61% of the cycles, 22% of them together, so that either is busy 91% of the
+// time, at 2.0 GHz (the power limit; 2.4 GHz nominal).  The same instructions without any memory
 // access, on random operands, run at 3.1e12 (b = 64), 4.4e12 (b = 32; the
 // kernel 3.9e12) and 5.5e12 (b = 16; 5.0e12) pairs/s.  v_mfma_f32_32x32x16_f16
 // was no faster there (2.9-3.1e12 at b = 64).

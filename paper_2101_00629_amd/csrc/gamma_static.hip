@@ -1,8 +1,9 @@
 // ka_gamma_apply_static: the raw fused kernel product with its scratch (split-K
-// partial sums, BF16 hi/lo parts of Y) in a file-scope device array instead of
+// partial sums, FP16 or BF16 parts of Y) in a file-scope device array instead of
 // a caller-provided or library-allocated workspace, for callers that cannot
 // allocate device memory (code under stream capture, serving loops that forbid
-// allocation).  The kernels are those of ka_gamma_apply.
+// allocation).  The kernels are those of ka_gamma_apply with as much scratch: a
+// product whose fastest route needs more takes the one of less scratch.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

@@ -67,8 +67,9 @@ struct NsTeam {
 };
 
 // Hessenberg reduction with the matrix in LDS: four threads per dot product (223
-// us on average in the solve for 50 collocation pairs; 339 us with one, sums by
-// shuffles and the matrix read a column at a time)
+// us on average in a solve for 30 collocation pairs, 16 x 14 x 12 elements, p = 2,
+// exponential, b = 16; 336 us with one, sums by shuffles and the matrix read a
+// column at a time)
 struct NsLdsTeam : NsTeam<kNsThreads> {
   double* part;
 };
