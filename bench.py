@@ -69,17 +69,18 @@ def peak_pairs(kernel):
     return VALU_SLOTS_PER_S / SLOTS[kernel]
 
 
-# HBM traffic of the FP32 kernel product per launch: rocprofv3 --pmc
-# FETCH_SIZE, then WRITE_SIZE, averaged over the product's launches in a run
-# of this workload, each scaled by what the same counter reads for a plain
-# 256 MiB device copy (FETCH x 2.0, WRITE x 1.0); the profiles under profiles/
-# hold the runs.  Valid only for the kernel source it was measured on.
+# HBM traffic of the FP32 kernel product per block product (pre-pass, product
+# and sum of the splits): rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, averaged
+# over the block products in a run of this workload, each scaled by what the same
+# counter reads for a plain 256 MiB device copy (FETCH x 2.0, WRITE x 1.0);
+# profiles/gamma_f16x3_traffic.md has the runs.  Valid only for the kernel source
+# it was measured on.
 # Algorithmic bytes per launch: every point's coordinates (16 B), Y row
 # (4 b B) and Z row (4 b B) once, plus the row and column scales.
 TRAFFIC = {
-    "cube20": {"gamma_src_sha256_16": "e9865e3b896f266a", "fetch_bytes": 36.85e6, "write_bytes": 54.48e6,
+    "cube20": {"gamma_src_sha256_16": "f48e34b26ca300f7", "fetch_bytes": 132.1e6, "write_bytes": 97.7e6,
                "algorithmic_bytes": 33.9e6},
-    "cube64": {"gamma_src_sha256_16": "e9865e3b896f266a", "fetch_bytes": 5.919e9, "write_bytes": 7.360e7,
+    "cube64": {"gamma_src_sha256_16": "f48e34b26ca300f7", "fetch_bytes": 6.839e9, "write_bytes": 1.659e8,
                "algorithmic_bytes": 287496 * (2 * 16 + 8 * 64 + 4)},
 }
 
@@ -95,6 +96,13 @@ def measured_traffic(name):
         return None
     return t["fetch_bytes"] + t["write_bytes"]
 
+
+# What `dtype` does not say of the kernel product's contraction
+CONTRACTION = {
+    "fp32": "FP32 values as pairs of FP16 parts (22 bits and a sign), 3 FP16 MFMAs, FP32 accumulation, FP64 totals; "
+            "what FP16's range does not hold in FP32",
+    "bf16x3": "Gaussian as fp32; exponential: values split hi + lo into BF16, 3 BF16 MFMAs, FP32 accumulation",
+}
 
 WORKLOADS = {
     "cube64": "unit cube p=2 64^3 (N=287496), Gaussian l=0.2, M=200, b=64, Galerkin-IBQ: one full K-L solve "
@@ -742,6 +750,7 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32" if args.precision == "fp32" else "bf16x3",
+        "contraction": CONTRACTION[args.precision],
         "data": "synthetic",
         "config": {"workload": WORKLOADS[name], "solves_per_step": len(probs), "tol": args.tol,
                    "precision": args.precision},
@@ -756,7 +765,7 @@ def main():
         nb = max(1, min(args.steps, 3))
         rb = measure(K, torch, name, "bf16x3", nb, 1, args.tol)
         line["split_bf16"] = {
-            "value": rb["pairs"] / rb["elapsed"], "unit": "pairs/s", "steps": nb,
+            "contraction": CONTRACTION["bf16x3"], "value": rb["pairs"] / rb["elapsed"], "unit": "pairs/s", "steps": nb,
             "solves_per_s": rb["nsolves"] / rb["elapsed"], "latency_ms": latency(rb["lat"]),
             "eig_err": {"max_floored_rel_err": rb["worst"], "bar": 1e-5,
                         "per_problem": {k: v["max_floored_rel_err"] for k, v in rb["eig"].items()}},
