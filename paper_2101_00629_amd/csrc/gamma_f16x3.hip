@@ -912,9 +912,22 @@ __device__ __forceinline__ double block_sum(double s, double* s_sum) {
 // could give most holds enough of |Gamma| |Y|; the rows, if the entries are many.
 // (N(0, 1) blocks of 287,496 x 64: a dozen entries in 50 row blocks get as far
 // as the check of the group, none further.)
+//
+// Where the columns are split, those of this item may all be far from a row and
+// their sum low for the boxes, but nothing beside that of another split.  So a
+// single column anywhere whose part of |Gamma| |Y| outweighs what this item and as
+// many others could lose is enough to leave a result as it is (`weighs`): the
+// column in the row's place (the row itself where rows and columns are the same
+// points), then the nearest of 16 in the group whose box is nearest.  Without this,
+// rows are done again in the items next to their own when correlation lengths are
+// short (us, without / with): b = 16, 5,280 points of a half cylinder, ell a 15th of
+// its height, 57 / 36; b = 32, 4,312 points of a quarter annulus, ell = 0.12, 96 /
+// 43; 11,968 points of it 111 / 95; b = 64, 85,184 points of the cube, ell = 0.1,
+// sines over the cube 12.4 / 3.1 ms.
 constexpr float kLostCut = 0x1p-19f;
 constexpr float kFarExponent = 86.f;   // from here on 2^-40 of a kernel value is below FP32's least, 2^-126
 constexpr int kEntries = 64;
+constexpr uint16_t kNoEntry = 0xffff;   // (an entry is below 256 rows times 64 vectors)
 
 struct Lossy {
   int rows, entries;
@@ -931,9 +944,9 @@ struct LossyShared {
 
 template <int KERNEL, int B, int RB>
 __device__ __forceinline__ Lossy lossy_results(const GammaLaunch& a, int64_t row0, int64_t c_begin, int64_t c_end,
-                                               int64_t g0, int64_t g1, const float* out, const float* s_lost,
-                                               const int* s_best, LossyShared<B>& sh, uint16_t* s_list,
-                                               uint16_t* s_entry) {
+                                               int64_t g0, int64_t g1, const float* out,
+                                               const float (*s_row)[64 * RB], float* s_lost, const int* s_best,
+                                               LossyShared<B>& sh, uint16_t* s_list, uint16_t* s_entry, bool rows) {
   constexpr int NT = B / 16, ROWS = 64 * RB;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, l16 = lane & 15;
   float v_size = 0.f;
@@ -961,6 +974,80 @@ __device__ __forceinline__ Lossy lossy_results(const GammaLaunch& a, int64_t row
   __syncthreads();
   float largest = 0.f;
   for (int v = 0; v < B; ++v) largest = fmaxf(largest, sh.size[v]);
+  auto value = [&](const float* x, int64_t c) {
+    float d = 0.f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float t = __builtin_fabsf(x[k] - a.xc[c * a.xc_stride + k]) * a.coord_scale;
+      d += KERNEL == KA_GAUSSIAN ? t * t : t;
+    }
+    return __builtin_amdgcn_exp2f(-d);
+  };
+  // the column in a row's place, and the least that a column has to add to a row's
+  // |Gamma| |Y| in a vector of size 1
+  auto in_place = [&](int i) { return (int64_t)((double)(row0 + i) * (double)a.nc / (double)a.nr); };
+  auto cut = [&](int i) { return (float)a.nsplit * kLostCut * s_lost[i] / largest; };
+  // leaves rows as they are that a column outweighs (s_lost 0); true if others are left
+  auto leave_rows = [&](bool left) {
+    const float* xr = a.xr + (left ? row0 + threadIdx.x : row0) * a.xr_stride;
+    const float x[3] = {xr[0], xr[1], xr[2]};
+    auto weighs = [&](int64_t c) {
+      const float e = value(x, c), least = cut(threadIdx.x);
+      int all = 1;
+      for (int v = 0; v < B; v += 16) {
+        float4 y[4];   // (all at once: one by one they are four waits)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y[u] = reinterpret_cast<const float4*>(a.Y + c * B + v)[u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float* size = &sh.size[v + 4 * u];   // (zero for vectors that do not count)
+          all &= (int)(e * __builtin_fabsf(y[u].x) >= least * size[0]) | (int)(size[0] == 0.f);
+          all &= (int)(e * __builtin_fabsf(y[u].y) >= least * size[1]) | (int)(size[1] == 0.f);
+          all &= (int)(e * __builtin_fabsf(y[u].z) >= least * size[2]) | (int)(size[2] == 0.f);
+          all &= (int)(e * __builtin_fabsf(y[u].w) >= least * size[3]) | (int)(size[3] == 0.f);
+        }
+      }
+      return all != 0;
+    };
+    const bool had = left;
+    if (left) left = !weighs(in_place(threadIdx.x));
+    if (a.nsplit > 1 && __syncthreads_or(left)) {
+      if (left) {
+        int64_t near = 0, at = 0;
+        float most = -1.f;
+        const int64_t step = (a.ngroups + 127) / 128;
+        for (int64_t g = 0; g < a.ngroups; g += step) {
+          const uniform_float* b = (const uniform_float*)(uintptr_t)(a.gbox + 8 * g);
+          float d = 0.f;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const float t = s_row[k][threadIdx.x], gap = fmaxf(fmaxf(b[k] - t, t - b[4 + k]), 0.f);
+            d += KERNEL == KA_GAUSSIAN ? gap * gap : gap;
+          }
+          const float v = __builtin_amdgcn_exp2f(-d) * b[7];
+          if (v > most) {
+            most = v;
+            near = g;
+          }
+        }
+        most = -1.f;
+#pragma unroll 4
+        for (int k = 0; k < 16; ++k) {
+          const int64_t c = near * kGroup + (k * (k + 1) / 2 * 29 & (kGroup - 1));
+          const float v = c < a.nc ? value(x, c) : -1.f;
+          if (v > most) {
+            most = v;
+            at = c;
+          }
+        }
+        left = !weighs(at);
+      }
+    }
+    if (had && !left) s_lost[threadIdx.x] = 0.f;
+    return __syncthreads_or(left) != 0;
+  };
+  const uint32_t word = threadIdx.x / 32, bit = threadIdx.x % 32;
+  if (rows && !leave_rows(threadIdx.x < ROWS && row0 + threadIdx.x < a.nr && s_lost[threadIdx.x % ROWS] > 0.f)) return {0, 0};
   float size[NT];   // of vectors 16 t + l16, the largest 1
   bool gap[NT];
 #pragma unroll
@@ -968,32 +1055,52 @@ __device__ __forceinline__ Lossy lossy_results(const GammaLaunch& a, int64_t row
     size[t] = largest > 0.f ? sh.size[16 * t + l16] / largest : 0.f;
     gap[t] = sh.gap[16 * t + l16] != 0;
   }
-  for (int k = 0; k < 4 * RB; ++k) {
-    const int i = wave * 16 * RB + 16 * (k / 4) + 4 * q + k % 4;
-    const bool in = row0 + i < a.nr;
-    const int64_t row = in ? row0 + i : a.nr - 1;
-    const double lost = in ? fabs(row_factor(a, row)) * (double)(kLostCut * s_lost[i]) : 0.0;
-    bool low[NT], all = lost > 0.0;
+  for (int rb = 0; rb < RB; ++rb) {
+    float z[4][NT];   // (all at once: row by row they are four waits)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      low[t] = fabs((double)out[row * B + 16 * t + l16]) < lost * (double)size[t];
-      all = all && (low[t] || size[t] == 0.f);
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = row0 + wave * 16 * RB + 16 * rb + 4 * q + r;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) z[r][t] = out[(row < a.nr ? row : a.nr - 1) * B + 16 * t + l16];
     }
-    const bool whole = (__ballot(all) >> (16 * q) & 0xffff) == 0xffff;
-    if (whole && l16 == 0) atomicOr(&sh.rows[i / 32], 1u << (i % 32));
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-      if (low[t] && gap[t] && !whole) {
-        const int at = atomicAdd(&sh.n, 1);
-        if (at < kEntries) s_entry[at] = (uint16_t)(i * B + 16 * t + l16);
-        atomicOr(&sh.some[i / 32], 1u << (i % 32));
+    for (int r = 0; r < 4; ++r) {
+      const int i = wave * 16 * RB + 16 * rb + 4 * q + r;
+      const bool in = row0 + i < a.nr;
+      const double lost = in ? fabs(row_factor(a, in ? row0 + i : a.nr - 1)) * (double)(kLostCut * s_lost[i]) : 0.0;
+      bool low[NT], all = lost > 0.0;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        low[t] = fabs((double)z[r][t]) < lost * (double)size[t];
+        all = all && (low[t] || size[t] == 0.f);
       }
+      const bool whole = (__ballot(all) >> (16 * q) & 0xffff) == 0xffff;
+      if (whole && l16 == 0) atomicOr(&sh.rows[i / 32], 1u << (i % 32));
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        if (low[t] && gap[t] && !whole) {
+          const int at = atomicAdd(&sh.n, 1);
+          if (at < kEntries) s_entry[at] = (uint16_t)(i * B + 16 * t + l16);
+          atomicOr(&sh.some[i / 32], 1u << (i % 32));
+        }
+    }
   }
   __syncthreads();
   const int found = sh.n;
   const bool many = found > kEntries;
+  // (many entries: the rows that have them)
+  if (many && !rows) (void)leave_rows(threadIdx.x < ROWS && (sh.some[threadIdx.x % ROWS / 32] >> bit & 1) != 0);
+  if (!many && (int)threadIdx.x < found) {
+    const int e = s_entry[threadIdx.x], i = e / B, vec = e % B;
+    const int64_t c = in_place(i);
+    const float* xr = a.xr + (row0 + i) * a.xr_stride;
+    const float x[3] = {xr[0], xr[1], xr[2]};
+    if (value(x, c) * __builtin_fabsf(a.Y[c * B + vec]) >= cut(i) * sh.size[vec]) s_entry[threadIdx.x] = kNoEntry;
+  }
+  __syncthreads();
   Lossy n = {0, 0};
   for (int k = 0; k < (many ? 0 : found); ++k) {
+    if (s_entry[k] == kNoEntry) continue;
     const int e = s_entry[k], i = e / B, vec = e % B;
     const int64_t c = (g0 + s_best[i]) * kGroup + threadIdx.x;
     double s = 0.0, x[3], z[3];
@@ -1011,15 +1118,18 @@ __device__ __forceinline__ Lossy lossy_results(const GammaLaunch& a, int64_t row
       ++n.entries;
     }
   }
+  if (many) {
+    if (threadIdx.x < ROWS && s_lost[threadIdx.x] == 0.f) atomicAnd(&sh.some[word], ~(1u << bit));
+    __syncthreads();
+  }
   int at = 0;
   uint32_t own = 0;
   for (int w = 0; w < ROWS / 32; ++w) {
-    const uint32_t word = sh.rows[w] | (many ? sh.some[w] : 0u);
-    if (w < (int)threadIdx.x / 32) at += __builtin_popcount(word);
-    if (w == (int)threadIdx.x / 32) own = word;
-    n.rows += __builtin_popcount(word);
+    const uint32_t bits = sh.rows[w] | (many ? sh.some[w] : 0u);
+    if (w < (int)word) at += __builtin_popcount(bits);
+    if (w == (int)word) own = bits;
+    n.rows += __builtin_popcount(bits);
   }
-  const uint32_t bit = threadIdx.x % 32;
   if (own >> bit & 1) s_list[at + __builtin_popcount(own & ((1u << bit) - 1))] = (uint16_t)threadIdx.x;
   __syncthreads();   // (also: what is done again has been written)
   return n;
@@ -1228,12 +1338,14 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
       whole = whole || (__ballot(all) >> (16 * q) & 0xffff) == 0xffff;
     }
   }
-  if (!look || !__syncthreads_or(whole || (some && (flags & kGaps)))) return true;
+  if (!look) return true;
+  const bool rows = __syncthreads_or(whole) != 0;
+  if (!rows && !((flags & kGaps) && __syncthreads_or(some))) return true;
   uint16_t* s_list = reinterpret_cast<uint16_t*>(&s_x[0][0]);
   constexpr size_t kPlace = sizeof(uint4) * kYRing * 2 * h16_entries<B>();
   static_assert(sizeof(LossyShared<B>) <= kPlace && sizeof(double) * 64 * B <= kPlace, "both take the place of Y's tiles");
-  const Lossy n = lossy_results<KERNEL, B, RB>(a, row0, c0s, c1s, g0, g1, out, s_lost, s_best,
-                                               *reinterpret_cast<LossyShared<B>*>(&s_y[0][0]), s_list, s_list + ROWS);
+  const Lossy n = lossy_results<KERNEL, B, RB>(a, row0, c0s, c1s, g0, g1, out, s_row, s_lost, s_best,
+                                               *reinterpret_cast<LossyShared<B>*>(&s_y[0][0]), s_list, s_list + ROWS, rows);
   if (4 * n.rows >= ROWS) return false;
   if (n.rows > 0)
     redo_rows<KERNEL, B>(a, row0, s_list, n.rows, c0s, c1s, reinterpret_cast<double(*)[16 * B]>(&s_y[0][0]), out);
