@@ -1232,9 +1232,9 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
     const int f = (int)flag_own;
     flags |= f & (kMarks - 1);
     size = max(size, __builtin_bit_cast(int, size_own));   // (not negative: in order as integers too)
-    if (f > kMarks * kFewMarks) {
-      atomicAdd(&s_marks, f / kMarks);
-    } else if (f >= kMarks) {
+    if (const int n = f / kMarks; n > kFewMarks) {   // (without the flags: what is counted as few is listed)
+      atomicAdd(&s_marks, n);
+    } else if (n > 0) {
       uint4 m[kGroup / 128];   // (all at once: word by word they are 16 waits)
 #pragma unroll
       for (int k = 0; k < kGroup / 128; ++k) m[k] = reinterpret_cast<const uint4*>(a.gmask + g * (kGroup / 32))[k];
