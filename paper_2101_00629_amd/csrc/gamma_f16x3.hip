@@ -80,7 +80,7 @@ constexpr int kPreThreads = 1024;           // of the pre-pass, one workgroup pe
 constexpr int kXEntries = 256;              // uint4 of column operands per tile
 constexpr float kLat = 64.f;                // 1 / spacing of the coordinate lattice
 
-constexpr int kFewColumns = 64;             // a group with no more columns that are not zero has them added in FP32
+constexpr int kFewColumns = 64;             // a group with no more columns that are not zero (half of it at most) has them added in FP32
 constexpr int kNoScale = 200;               // "scale" of a vector that is zero in a group
 
 enum { kOffLattice = 1, kGaps = 2, kMarks = 4 };   // flags of a column group, and kMarks times its columns in FP32
@@ -279,7 +279,10 @@ __device__ __forceinline__ void split16_group(const GammaLaunch& a, int kernel, 
   int count = 0;
 #pragma unroll
   for (int w = 0; w < G / 32; ++w) count += __builtin_popcount(sh.nz[w]);
-  const bool few = count <= kFewColumns;
+  // (not a short last group: its box is that of its few columns.  b = 64, 100,000 x
+  // 568 takes 58 us so, and 89 with the last 56 columns in FP32)
+  const int cols = (int)(a.nc - g * G < G ? a.nc - g * G : G);
+  const bool few = count <= kFewColumns && 2 * count <= cols;
   auto exact_word = [&](int w) { return sh.bad[w] | sh.point[w] | (few ? sh.nz[w] : 0u); };
   if (threadIdx.x < G / 32) a.gmask[g * (G / 32) + threadIdx.x] = exact_word(threadIdx.x);
   if (threadIdx.x < 2) a.ggap[2 * g + threadIdx.x] = sh.gap[threadIdx.x];
