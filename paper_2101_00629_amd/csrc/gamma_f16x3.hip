@@ -1207,6 +1207,7 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
   __shared__ float s_lost[ROWS];
   __shared__ int s_best[ROWS];
   __shared__ int s_flags, s_marks, s_size, s_look, s_cnt[4], s_few[kFewMarks];
+  __shared__ uint32_t s_gap[2];
   const int64_t row0 = rblk * ROWS;
   const int64_t c0s = (int64_t)split * a.cols_per_split;
   const int64_t c1s = c0s + a.cols_per_split < a.nc ? c0s + a.cols_per_split : a.nc;
@@ -1218,6 +1219,7 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
   const int64_t g_own = g0 + threadIdx.x < g1 ? g0 + threadIdx.x : g0;
   float flag_own = a.gbox[8 * g_own + 3], size_own = a.gbox[8 * g_own + 7];
   if (threadIdx.x == 0) s_flags = s_marks = s_size = s_look = 0;   // (gram_rows has a barrier)
+  if (threadIdx.x < 2) s_gap[threadIdx.x] = 0;
   double cl[3];
   launch_centre(a, cl);
   float c0, c1, c2;
@@ -1292,6 +1294,9 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
   __syncthreads();
   const bool look = s_look || (flags & kGaps);
   if (look) {
+    if (flags & kGaps)
+      for (int64_t g = 2 * g0 + threadIdx.x; g < 2 * g1; g += kThreads)
+        if (const uint32_t gaps = a.ggap[g]) atomicOr(&s_gap[g & 1], gaps);
     if (threadIdx.x < ROWS) {
       float x[3];
 #pragma unroll
@@ -1320,7 +1325,8 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
     __syncthreads();
   }
   float* out = a.nsplit > 1 ? a.partial + (size_t)split * a.nr * B : a.Z;
-  bool some = false, whole = false;
+  bool some = false, whole = false;   // (a low entry is of interest in a vector with gaps only)
+  const uint32_t gaps = look ? s_gap[0] : 0u, gaps_hi = look && B == 64 ? s_gap[1] : 0u;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int r0 = wave * 16 * RB + 16 * rb + 4 * q;
@@ -1333,7 +1339,7 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
 #pragma unroll
         for (int t = 0; t < B / 16; ++t) {
           const bool low = fabs(tot[rb][t][r]) < lost;
-          some = some || (low && 16 * t + (lane & 15) < a.nv);   // (vectors that do not count are zero)
+          some = some || (low && ((t < 2 ? gaps : gaps_hi) >> (16 * (t & 1) + (lane & 15)) & 1) != 0);
           all = all && low;
           out[row * B + 16 * t + (lane & 15)] = (float)(f * tot[rb][t][r]);
         }
