@@ -331,7 +331,12 @@ __device__ __forceinline__ void split16_group(const GammaLaunch& a, int kernel, 
                         pack_h2(1.f, vec < B ? s_up[vec] : 0.f));
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const float l = p.l[k] * kLat, b = -l * (2.f * p.h[k] + p.l[k]);
+      const float l = p.l[k] * kLat;
+      float b = -l * (2.f * p.h[k] + p.l[k]);
+      // (one value for its part and for what that leaves: a product rounded straight
+      // to FP16 in the one and by way of FP32 in the other is a last place off, 2^-13
+      // in the exponent, for one column in some thousands)
+      asm("" : "+v"(b));
       const float b1 = b - half_of(b);
       dst[16 * (k + 1)] = make_uint4(pack_h2(l, l - half_of(l)), pack_h2(p.h[k] / kLat, p.h[k] / kLat), pack_h2(l, b),
                                      pack_h2(b1, b1 - half_of(b1)));
