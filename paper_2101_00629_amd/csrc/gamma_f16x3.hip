@@ -915,7 +915,7 @@ __device__ __forceinline__ double block_sum(double s, double* s_sum) {
 // Which stored results may have lost what matters: entries (i B + vector, i the
 // row's place) into s_entry, whole rows into s_list.  A low result is not
 // cancellation if no vector of the row comes out larger for its size (a hole
-// between scattered columns): the row.  In a vector with zeros or very small
+// between scattered columns; results that are not finite don't count): the row.  In a vector with zeros or very small
 // entries the near columns may be among these: the entry, unless the group that
 // could give most holds enough of |Gamma| |Y|; the rows, if the entries are many.
 // (N(0, 1) blocks of 287,496 x 64: a dozen entries in 50 row blocks get as far
@@ -1076,13 +1076,14 @@ __device__ __forceinline__ Lossy lossy_results(const GammaLaunch& a, int64_t row
       const int i = wave * 16 * RB + 16 * rb + 4 * q + r;
       const bool in = row0 + i < a.nr;
       const double lost = in ? fabs(row_factor(a, in ? row0 + i : a.nr - 1)) * (double)(kLostCut * s_lost[i]) : 0.0;
-      bool low[NT], all = lost > 0.0;
+      bool low[NT], all = lost > 0.0, any = false;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         low[t] = fabs((double)z[r][t]) < lost * (double)size[t];
-        all = all && (low[t] || size[t] == 0.f);
+        any = any || low[t];
+        all = all && (low[t] || size[t] == 0.f || !finite_bits(z[r][t]));
       }
-      const bool whole = (__ballot(all) >> (16 * q) & 0xffff) == 0xffff;
+      const bool whole = (__ballot(all) >> (16 * q) & 0xffff) == 0xffff && (__ballot(any) >> (16 * q) & 0xffff) != 0;
       if (whole && l16 == 0) atomicOr(&sh.rows[i / 32], 1u << (i % 32));
 #pragma unroll
       for (int t = 0; t < NT; ++t)
@@ -1290,10 +1291,14 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      bool all = true;
+      bool all = true, any = false;   // (a result that is not finite says nothing of the others)
 #pragma unroll
-      for (int t = 0; t < B / 16; ++t) all = all && fabs(tot[rb][t][r]) < largest;
-      low = low || all;
+      for (int t = 0; t < B / 16; ++t) {
+        const double z = fabs(tot[rb][t][r]);
+        any = any || z < largest;
+        all = all && (z < largest || !(z < INFINITY));
+      }
+      low = low || (all && any);
     }
   if (__any(low && (lane & 15) < a.nv) && lane == 0) s_look = 1;
   __syncthreads();
@@ -1338,18 +1343,19 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int64_t row = row0 + r0 + r;
-      bool all = row < a.nr;
+      bool all = row < a.nr, any = false;
       if (row < a.nr) {
         const double f = row_factor(a, row), lost = look ? (double)(kLostCut * s_lost[r0 + r]) : 0.0;
 #pragma unroll
         for (int t = 0; t < B / 16; ++t) {
           const bool low = fabs(tot[rb][t][r]) < lost;
           some = some || (low && ((t < 2 ? gaps : gaps_hi) >> (16 * (t & 1) + (lane & 15)) & 1) != 0);
-          all = all && low;
+          any = any || low;
+          all = all && (low || !(fabs(tot[rb][t][r]) < INFINITY));
           out[row * B + 16 * t + (lane & 15)] = (float)(f * tot[rb][t][r]);
         }
       }
-      whole = whole || (__ballot(all) >> (16 * q) & 0xffff) == 0xffff;
+      whole = whole || ((__ballot(all) >> (16 * q) & 0xffff) == 0xffff && (__ballot(any) >> (16 * q) & 0xffff) != 0);
     }
   }
   if (!look) return true;
