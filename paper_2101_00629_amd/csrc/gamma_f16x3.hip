@@ -30,7 +30,9 @@
 //   was lost (lossy_results), are done again; where that is a quarter of an item's
 //   rows, all of it.
 // So what is lost is below 2^-19 of a result, or below 2^-126 |Y| (groups at
-// exponents past 86, where the loss is below FP32's least value).
+// exponents past 86, where the loss is below FP32's least value).  Not seen: a low
+// result in a vector without very small entries, in a row whose other results are
+// not low (a row without near columns, and at the nearest of them a small entry).
 //
 // Exponents (Gaussian).  16 x 16 exponents -|x - y|^2 come from one
 // v_mfma_f32_16x16x32_f16.  Coordinates (scaled, relative to the launch's
@@ -1335,30 +1337,38 @@ __device__ __forceinline__ bool gamma_h16_item(const GammaLaunch& a, int64_t rbl
     __syncthreads();
   }
   float* out = a.nsplit > 1 ? a.partial + (size_t)split * a.nr * B : a.Z;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = row0 + wave * 16 * RB + 16 * rb + 4 * q + r;
+      if (row < a.nr) {
+        const double f = row_factor(a, row);
+#pragma unroll
+        for (int t = 0; t < B / 16; ++t) out[row * B + 16 * t + (lane & 15)] = (float)(f * tot[rb][t][r]);
+      }
+    }
+  if (!look) return true;
   bool some = false, whole = false;   // (a low entry is of interest in a vector with gaps only)
-  const uint32_t gaps = look ? s_gap[0] : 0u, gaps_hi = look && B == 64 ? s_gap[1] : 0u;
+  const uint32_t gaps = s_gap[0], gaps_hi = B == 64 ? s_gap[1] : 0u;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int r0 = wave * 16 * RB + 16 * rb + 4 * q;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t row = row0 + r0 + r;
-      bool all = row < a.nr, any = false;
-      if (row < a.nr) {
-        const double f = row_factor(a, row), lost = look ? (double)(kLostCut * s_lost[r0 + r]) : 0.0;
+      const double lost = row0 + r0 + r < a.nr ? (double)(kLostCut * s_lost[r0 + r]) : 0.0;
+      bool all = true, any = false;
 #pragma unroll
-        for (int t = 0; t < B / 16; ++t) {
-          const bool low = fabs(tot[rb][t][r]) < lost;
-          some = some || (low && ((t < 2 ? gaps : gaps_hi) >> (16 * (t & 1) + (lane & 15)) & 1) != 0);
-          any = any || low;
-          all = all && (low || !(fabs(tot[rb][t][r]) < INFINITY));
-          out[row * B + 16 * t + (lane & 15)] = (float)(f * tot[rb][t][r]);
-        }
+      for (int t = 0; t < B / 16; ++t) {
+        const double z = fabs(tot[rb][t][r]);
+        const bool low = z < lost;
+        some = some || (low && ((t < 2 ? gaps : gaps_hi) >> (16 * (t & 1) + (lane & 15)) & 1) != 0);
+        any = any || low;
+        all = all && (low || !(z < INFINITY));
       }
       whole = whole || ((__ballot(all) >> (16 * q) & 0xffff) == 0xffff && (__ballot(any) >> (16 * q) & 0xffff) != 0);
     }
   }
-  if (!look) return true;
   const bool rows = __syncthreads_or(whole) != 0;
   if (!rows && !((flags & kGaps) && __syncthreads_or(some))) return true;
   uint16_t* s_list = reinterpret_cast<uint16_t*>(&s_x[0][0]);
