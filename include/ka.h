@@ -56,13 +56,17 @@ enum ka_domain { KA_BOX = 0, KA_QUARTER_ANNULUS = 1, KA_NURBS = 2 /* general sin
 enum ka_kernel { KA_GAUSSIAN = 0, /* sigma^2 exp(-|x-y|_2^2 / ell^2) */
                  KA_EXP_L1 = 1    /* sigma^2 exp(-|x-y|_1 / ell)     */ };
 /* Precision of the kernel product.  Every entry of Z is within 1e-5 (KA_FP32) or 6e-5
- * (KA_BF16X3) of |Gamma| |Y|, besides what rounding the points to FP32 does to Gamma.
+ * (KA_BF16X3) of |Gamma| |Y|, besides what rounding scaled points to FP32 does to Gamma.
  * KA_FP32    kernel values in FP32, FP32 MFMA contraction.  Large products contract
  *            pairs of FP16 parts: 22 bits and a sign of each value of Gamma and Y (FP32
  *            has 24), 3 FP16 MFMAs, FP32 accumulation of 16 of them, FP64 totals.  The
  *            rounding is smaller than that of FP32 MFMAs all the same; what the range
  *            of FP16 does not hold (values not finite or far below the others of their
- *            512 columns) is formed in FP32.
+ *            512 columns) is formed in FP32.  Left is 2^-40 of the largest |Y| times
+ *            the largest Gamma that the bounding box of 512 columns allows: it can pass
+ *            1e-5 where a row has no column near (Gamma below 2^-9 of that) and the
+ *            entries of a vector there are 2^-9 of its largest or less, while other
+ *            vectors of the row are larger.
  * KA_BF16X3  kernel values in FP32, split hi + lo into BF16, 3 BF16 MFMAs, FP32
  *            accumulation; large Gaussian products as KA_FP32, which is faster there
  *            and closer. */
